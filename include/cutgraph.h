@@ -95,7 +95,9 @@ typedef enum {
 typedef enum {
     CUT_F64 = 0,            /* double operands, double products and sums */
     CUT_F32C = 1,           /* float operands and products; compensated sums
-                               (error-free product by FMA + two-sum), double result */
+                               (error-free product by FMA + two-sum), double result.
+                               Large Majorana passes sum in double as CUT_F32X does:
+                               no less accurate, and their results are the same */
     CUT_F32X = 2,           /* float operands; products and sums in double (products
                                of two floats and a small integer factor are exact) */
     CUT_F32 = 3             /* float operands, products and plain float sums
@@ -480,7 +482,9 @@ cut_status cut_graph_set_tiling(cut_graph_t g, int64_t long_records, int64_t chu
  * CUT_F32X and `allow_other_float` != 0, over both compensated float modes;
  * applies the fastest tiling to the graph (a candidate must beat the best so
  * far, starting with the graph's current tiling, by at least 2 %) and returns
- * the choice.  It allocates temporary operand buffers (zero-filled) and
+ * the choice.  Large Majorana passes (FP64, CUT_F32C, CUT_F32X) contract in
+ * triple space and use no tiling: the graph's current one stays then.  It
+ * allocates temporary operand buffers (zero-filled) and
  * synchronises the device.  Results are cached per (nsets, nops, precision,
  * allow_other_float).
  * Errors: CUT_E_INVAL, CUT_E_NOMEM, CUT_E_DEVICE. */

@@ -140,6 +140,7 @@ PassArgs apply_args(Graph& g, int32_t which, int32_t precision, int64_t nsets, i
     p.accumulate = (flags & CUT_ACCUMULATE) ? 1 : 0;
     p.scale = 1.0;
     *part_bytes = which == CUT_GRAPH_FLOW ? forward_partial_bytes(g, p.nsets, p.nops, precision) : 0;
+    p.part_bytes = *part_bytes;
     return p;
 }
 

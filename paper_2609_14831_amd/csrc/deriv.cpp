@@ -189,6 +189,7 @@ extern "C" cut_status cut_graph_jvp(cut_graph_t hd, int32_t kind, double delta, 
     p.nops = (int32_t)nops;
     p.precision = precision;
     p.scale = 1.0;
+    p.part_bytes = pb;
     p.lda = nsets;
     // dy = apply(deta, x) + apply(eta, dx)
     p.y = dy;
@@ -248,6 +249,8 @@ extern "C" cut_status cut_graph_vjp(cut_graph_t hd, int32_t kind, double delta, 
     const size_t i_eta = lay.eta, i_w32 = lay.w32, i_x32 = lay.x32, i_geta = lay.geta, i_tmp = lay.tmp;
     char* base = (char*)g.ws_deriv.need(cv.total, "cut_graph_vjp");
     auto at = [&](size_t i) { return (void*)(base + cv.offs[i]); };
+    const size_t pb = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, precision);
+    double* part = pb ? (double*)g.ws_part.need(pb, "cut_graph_vjp (partial rows)") : nullptr;
 
     const void* wo = w;
     int64_t ldwo = ldw;
@@ -261,6 +264,7 @@ extern "C" cut_status cut_graph_vjp(cut_graph_t hd, int32_t kind, double delta, 
     p.nops = (int32_t)nops;
     p.precision = precision;
     p.scale = 1.0;
+    p.part_bytes = pb;
     if (g_x) {
         // g_x (=|+=) L(eta)^T w: the record copy grouped by right input j
         void* eta = at(i_eta);
@@ -273,7 +277,7 @@ extern "C" cut_status cut_graph_vjp(cut_graph_t hd, int32_t kind, double delta, 
         p.y = g_x;
         p.ldy = ldgx;
         p.accumulate = acc ? 1 : 0;
-        launch_pass(MODE_BCAST, EPI_Y, p, s);
+        launch_adjoint_x(g, p, part, s);
     }
     if (g_h) {
         // geta = sum over the records grouped by left input i of c sum_op w_k x_j,
@@ -294,7 +298,7 @@ extern "C" cut_status cut_graph_vjp(cut_graph_t hd, int32_t kind, double delta, 
         p.y = geta;
         p.ldy = nsets;
         p.accumulate = 0;
-        launch_pass(MODE_REDOPS, EPI_Y, p, s);
+        launch_adjoint_eta(g, p, part, s);
         if (!acc) launch_zero2d(g_h, ldgh, N, nsets, s);
         eval_generator_vjp(g, kind, delta, (int32_t)nsets, h, ldh, geta, nsets, g_h, ldgh,
                            stencil_generator(kind) ? (double*)at(i_tmp) : nullptr, s);

@@ -113,7 +113,8 @@ struct FlowBufs {
     int32_t* nsteps;
     int32_t* step;
     int32_t* flag;
-    double* part;   // tile partial slots (null when the tile path is not taken)
+    double* part;   // partial rows of the forward pass (null: none needed)
+    size_t part_bytes;
     double* zp;     // the state with its sets in flow order (see cut_flow_integrate)
     int32_t* perm;  // flow order: position q holds caller set perm[q]
 };
@@ -188,6 +189,7 @@ static FlowBufs flow_bufs(Graph& g, int64_t nsets, int64_t nops, int prec, size_
     f.step = (int32_t*)(b + L.st);
     f.flag = (int32_t*)(b + L.fl);
     f.part = L.part_bytes ? (double*)(b + L.part) : nullptr;
+    f.part_bytes = L.part_bytes;
     f.zp = (double*)(b + L.zp);
     f.perm = (int32_t*)(b + L.perm);
     if (extra_ptr) *extra_ptr = b + L.ex;
@@ -294,6 +296,7 @@ static void enqueue_step(const StepPlan& P, hipStream_t s, PassTimer* tm = nullp
         p.gmax = 64 >> g.bchunk;  // the tiling's B-chunk
         p.narrow = P.narrow;
         p.gfloor = P.gfloor;
+        p.part_bytes = P.fb.part_bytes;
         if (tm) tm->mark(0, s);
         const size_t nr = std::max<size_t>(1, P.ranges.size());
         for (size_t r = 0; r < nr; ++r) {
@@ -580,8 +583,8 @@ extern "C" cut_status cut_flow_integrate(cut_graph_t h, const cut_flow_params* p
 //   geta   = adjoint-eta pass (i-grouped records) of (mu, Z)
 //   u_h   += eta'(Z_h)^T geta
 static void jt(Graph& g, const cut_flow_params* p, int32_t nsets, int32_t nops, const double* Z, const double* mu,
-               double* u, double* eta, double* geta, double* tmp, const int32_t* nsteps, const int32_t* step,
-               hipStream_t s) {
+               double* u, double* eta, double* geta, double* tmp, const FlowBufs& fb, hipStream_t s) {
+    const int32_t *nsteps = fb.nsteps, *step = fb.step;
     const int64_t cols = (int64_t)nops * nsets;
     eval_generator(g, p->generator, p->delta, nsets, Z, cols, eta, nsets, false, nsteps, step, s);
     PassArgs a{};
@@ -598,7 +601,8 @@ static void jt(Graph& g, const cut_flow_params* p, int32_t nsets, int32_t nops, 
     a.ldb = cols;
     a.y = u;
     a.ldy = cols;
-    launch_pass(MODE_BCAST, EPI_Y, a, s);
+    a.part_bytes = fb.part_bytes;
+    launch_adjoint_x(g, a, fb.part, s);
     a.csr = &g.csr[0][2];
     a.A = mu;
     a.lda = cols;
@@ -606,7 +610,7 @@ static void jt(Graph& g, const cut_flow_params* p, int32_t nsets, int32_t nops, 
     a.ldb = cols;
     a.y = geta;
     a.ldy = nsets;
-    launch_pass(MODE_REDOPS, EPI_Y, a, s);
+    launch_adjoint_eta(g, a, fb.part, s);
     eval_generator_vjp(g, p->generator, p->delta, nsets, Z, cols, geta, nsets, u, cols, tmp, s);
 }
 
@@ -671,16 +675,16 @@ extern "C" cut_status cut_flow_adjoint(cut_graph_t h, const cut_flow_params* p, 
                 // u4 = J(Z4)^T [ds/6 lam]
                 launch_adj_combine(g.N, (int32_t)cols, (int32_t)nsets, fb.nsteps, fb.step, lambda, nullptr, lam_new,
                                    mu, ds / 6.0, 0.0, 1, s);
-                jt(g, p, (int32_t)nsets, (int32_t)nops, Zs[3], mu, u, eta, geta, tmp, fb.nsteps, fb.step, s);
+                jt(g, p, (int32_t)nsets, (int32_t)nops, Zs[3], mu, u, eta, geta, tmp, fb, s);
                 launch_adj_combine(g.N, (int32_t)cols, (int32_t)nsets, fb.nsteps, fb.step, lambda, u, lam_new, mu,
                                    ds / 3.0, ds, 0, s);
-                jt(g, p, (int32_t)nsets, (int32_t)nops, Zs[2], mu, u, eta, geta, tmp, fb.nsteps, fb.step, s);
+                jt(g, p, (int32_t)nsets, (int32_t)nops, Zs[2], mu, u, eta, geta, tmp, fb, s);
                 launch_adj_combine(g.N, (int32_t)cols, (int32_t)nsets, fb.nsteps, fb.step, lambda, u, lam_new, mu,
                                    ds / 3.0, 0.5 * ds, 0, s);
-                jt(g, p, (int32_t)nsets, (int32_t)nops, Zs[1], mu, u, eta, geta, tmp, fb.nsteps, fb.step, s);
+                jt(g, p, (int32_t)nsets, (int32_t)nops, Zs[1], mu, u, eta, geta, tmp, fb, s);
                 launch_adj_combine(g.N, (int32_t)cols, (int32_t)nsets, fb.nsteps, fb.step, lambda, u, lam_new, mu,
                                    ds / 6.0, 0.5 * ds, 0, s);
-                jt(g, p, (int32_t)nsets, (int32_t)nops, Zs[0], mu, u, eta, geta, tmp, fb.nsteps, fb.step, s);
+                jt(g, p, (int32_t)nsets, (int32_t)nops, Zs[0], mu, u, eta, geta, tmp, fb, s);
                 launch_adj_combine(g.N, (int32_t)cols, (int32_t)nsets, fb.nsteps, fb.step, lambda, u, lam_new,
                                    nullptr, 0.0, 0.0, 0, s);
                 launch_copy_active(g.N, (int32_t)cols, (int32_t)nsets, fb.nsteps, fb.step, lam_new, lambda, s);

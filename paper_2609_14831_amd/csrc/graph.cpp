@@ -134,6 +134,7 @@ Graph::~Graph() {
     dev_free(st_p);
     tiles.release();
     qb.release();
+    tri.release();
     ws.release();
     ws_small.release();
     ws_part.release();
@@ -1097,6 +1098,7 @@ extern "C" cut_status cut_graph_load(const char* path, int32_t dev, uint32_t fla
                 g->max_lds = lds;
         }
         if (!pb) build_tiles(*g, hg, code);
+        build_triples(*g, hg);
         HIP_CHECK(hipDeviceSynchronize());
         HIP_CHECK(hipSetDevice(prev));
         *out = (cut_graph_t)g;

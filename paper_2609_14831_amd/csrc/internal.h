@@ -251,6 +251,19 @@ struct QuadBlockPlan {
     void release();
 };
 
+// Triple-space form of the Majorana bracket (triples.hip): the table of rows
+// tau + w with the sign of sorting w into tau from behind, tau the triples in
+// lexicographic order followed by the single modes.
+struct TriPlan {
+    bool ok = false;
+    int32_t m = 0, nq = 0, nt = 0, ntau = 0;  // modes, quadratic rows, triples, triples + modes
+    int32_t ntp = 0;                          // row stride of the table
+    double c = 0.0;                           // common factor of the records
+    uint32_t* tab = nullptr;                  // device [modes, padded][ntp]
+    uint64_t* tmask = nullptr;                // device [nt]
+    void release();
+};
+
 // Device work area of a graph handle.  It is sized only by reservation calls
 // (cut_graph_reserve, and the tiling calls that re-size it for the shapes
 // reserved so far); the computing entry points take their share with need(),
@@ -306,6 +319,7 @@ struct Graph {
     TilePlan tiles;
     int use_tiles = 0;
     QuadBlockPlan qb;
+    TriPlan tri;
     int use_quadblocks = 0;
     uint64_t tiling_gen = 0;         // bumped whenever task lists are rebuilt
     int use_chunks = 1;
@@ -367,6 +381,7 @@ struct PassArgs {
     // lane groups of the segment kernel span at least this many sets (a
     // compacted flow keeps the widths, hence the sums, of its full layout)
     int32_t gfloor = 1;
+    size_t part_bytes = 0;          // partial-row bytes the caller provides to launch_forward
     int32_t precision;              // cut_precision
     const int32_t* nsteps;          // device [nsets] or null (all active)
     const int32_t* step;            // device scalar or null
@@ -400,6 +415,21 @@ size_t tile_partial_bytes(const Graph& g, int32_t nsets, int32_t nops);
 bool quadblocks_usable(const Graph& g, int32_t nsets, int32_t nops, int32_t precision);
 void launch_forward(const Graph& g, int epi, const PassArgs& a, double* partials, hipStream_t s);
 bool forward_set_ranges(const Graph& g, const PassArgs& a);
+// partial-row bytes of the passes over the records alone (the smallest area a
+// forward pass of this shape runs in)
+size_t record_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_t precision);
+
+// triple-space passes of Majorana graphs: plan, partial rows, whether a pass
+// may take the route, and the pass  out = sign * sum_{r < nred} L(A_r) B_r
+// (A and B advance by nsets columns per r) with the epilogue of `a`
+void build_triples(Graph& g, const HostGraph& hg);
+size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops);
+bool triples_usable(const Graph& g, const PassArgs& a);
+// the two transposed actions of E_L (a: the pass over the reverse orientation),
+// as brackets where triples_usable, with `part` as the forward pass has it
+void launch_adjoint_x(const Graph& g, const PassArgs& a, double* part, hipStream_t s);
+void launch_adjoint_eta(const Graph& g, const PassArgs& a, double* part, hipStream_t s);
+void launch_triples(const Graph& g, int epi, const PassArgs& a, int nred, double sign, double* part, hipStream_t s);
 // rows x (nops x nsets) state: dst[r][op][s] = src[r][op][perm[s]] (inverse:
 // dst[r][op][perm[s]] = src[r][op][s])
 void launch_permute_sets(const double* src, double* dst, int64_t rows, int32_t nops, int32_t nsets,

@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "device.h"
 #include "internal.h"
 
 namespace cut {
@@ -165,52 +166,17 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// Gather of one element of a row through a buffer resource built (on the
-// scalar unit) from the uniform row address: the lane's byte offset is the only
-// per-lane operand, so a gather costs no vector address arithmetic.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* row, int64_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(row), (short)0, (int)bytes, 0x00020000);
-}
-template <class T>
-__device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, uint32_t voff, int32_t soff) {
-    if constexpr (sizeof(T) == 4) {
-        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, soff, 0));
-    } else {
-        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, soff, 0));
-    }
-}
-
 __device__ inline bool set_active(const KArgs& a, int s) {
     if (s >= a.nsets) return false;
     if (a.nsteps == nullptr) return true;
     return a.nsteps[s] > *a.step;
 }
 
-// Classic RK4 stage combination for the NOPS operand values f of row `seg`,
-// set s: stage 0 starts the accumulator, 1-2 add to it, 3 finishes the step;
-// the next stage operand is written (float or double shadow) together with the
-// FP64 Hamiltonian column.  z and the accumulator are touched once per stage:
-// streamed with non-temporal hints so they do not displace gathered rows.
-// One state element idx with right-hand side f at stage a.stage: updates the
-// accumulator (and, at the last stage, z) and returns the next stage state.
+// Classic RK4 stage combination for the NOPS operand values v of row `seg`,
+// set s: the next stage operand is written (float or double shadow) together
+// with the FP64 Hamiltonian column.
 __device__ inline double rk_combine(const KArgs& a, int64_t idx, double f) {
-    const double ds = a.ds;
-    const double zk = __builtin_nontemporal_load(a.z + idx);
-    double nxt;
-    if (a.stage == 0) {
-        __builtin_nontemporal_store(zk + (ds / 6.0) * f, a.acc + idx);
-        nxt = zk + 0.5 * ds * f;
-    } else if (a.stage == 1) {
-        __builtin_nontemporal_store(__builtin_nontemporal_load(a.acc + idx) + (ds / 3.0) * f, a.acc + idx);
-        nxt = zk + 0.5 * ds * f;
-    } else if (a.stage == 2) {
-        __builtin_nontemporal_store(__builtin_nontemporal_load(a.acc + idx) + (ds / 3.0) * f, a.acc + idx);
-        nxt = zk + ds * f;
-    } else {
-        nxt = __builtin_nontemporal_load(a.acc + idx) + (ds / 6.0) * f;
-        __builtin_nontemporal_store(nxt, a.z + idx);
-    }
-    return nxt;
+    return rk_combine(a.stage, a.ds, a.z, a.acc, idx, f);
 }
 
 template <int NOPS, class T>
@@ -1486,6 +1452,11 @@ size_t chunk_partial_bytes(const Graph& g, int32_t nsets, int32_t nops) {
 static bool quad_and_tiles(const Graph& g, int32_t nsets, int32_t nops, int32_t precision);
 
 size_t forward_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_t precision) {
+    const size_t b = record_partial_bytes(g, nsets, nops, precision);
+    return precision == CUT_F32 ? b : std::max(b, triples_partial_bytes(g, nsets, nops));
+}
+
+size_t record_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_t precision) {
     // the chunk plan's rows are always needed: a launch over part of the sets
     // runs the plain chunked form whatever the tiling
     const size_t chunk = chunk_partial_bytes(g, nsets, nops);
@@ -1816,6 +1787,10 @@ void launch_forward(const Graph& g, int epi, const PassArgs& a_in, double* parti
     if (epi == EPI_ETA || a.csr != &g.csr[0][0] || partials == nullptr || cpass_usable(MODE_BCAST, epi, a) ||
         cshort_usable(MODE_BCAST, epi, a)) {
         launch_pass(MODE_BCAST, epi, a, s);
+        return;
+    }
+    if (triples_usable(g, a)) {
+        launch_triples(g, epi, a, 1, 1.0, partials, s);
         return;
     }
     const bool ranged = a.narrow || (a.s1 > 0 && (a.s0 != 0 || a.s1 != a.nsets));

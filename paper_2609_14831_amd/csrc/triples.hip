@@ -1,0 +1,450 @@
+// Triple-space contraction of the Majorana bracket: the plan built and checked
+// at load, the combine of the partial rows with the pass's epilogue, and the
+// launch (Sec. 2.2 Eq. graph-actions; Sec. 2.4 for the transposed uses).
+//
+// The plan is accepted only if the compiled records of E_L are exactly the
+// records of the bracket in the kernels' form, factor by factor, so the
+// contraction evaluates the compiled graph and nothing else.
+//
+// The bracket's structure constants c(k, i, j) are totally antisymmetric, so
+// the transposed actions are brackets too:
+//   sum_k,i c(k, i, j) e_i w_k = -L(e) w  at j,
+//   sum_k,j c(k, i, j) w_k x_j =  L(x) w  at i.
+#include <algorithm>
+#include <atomic>
+#include <cmath>
+#include <thread>
+#include <unordered_map>
+#include <vector>
+
+#include "triples_kernel.h"
+
+namespace cut {
+
+void TriPlan::release() {
+    if (tab) (void)hipFree(tab);
+    if (tmask) (void)hipFree(tmask);
+    tab = nullptr;
+    tmask = nullptr;
+    ok = false;
+}
+
+static inline int above(uint64_t set, int q) { return __builtin_popcountll(set & ~((2ull << q) - 1)) & 1; }
+
+// Sign of the record (target K; left I, right J) of the bracket in the form of
+// the kernels, 0 when there is no such record.
+static int record_sign(uint64_t K, uint64_t I, uint64_t J) {
+    if ((I ^ J) != K) return 0;
+    const int di = __builtin_popcountll(I), dj = __builtin_popcountll(J), dk = __builtin_popcountll(K);
+    auto low = [](uint64_t x) { return __builtin_ctzll(x); };
+    if (dk == 2 && di == dj && (di == 2 || di == 4)) {
+        // t = I & J, one mode of K on each side: + sigma(t,u) sigma(t,v) when u (the lower) is on the left
+        const uint64_t t = I & J;
+        const int u = low(I & ~t), v = low(J & ~t);
+        const int flip = (above(t, u) ^ above(t, v)) ^ (u < v ? 0 : 1);
+        return flip ? -1 : 1;
+    }
+    if (dk == 4 && di + dj == 6 && (di == 2 || di == 4)) {
+        const uint64_t Q = di == 2 ? I : J, F = di == 2 ? J : I;  // quadratic and quartic operand
+        const uint64_t t = K & F;
+        if (__builtin_popcountll(t) != 3) return 0;
+        const int w = low(K & ~t), q = low(F & ~t);
+        if (Q != ((1ull << w) | (1ull << q))) return 0;
+        // generator quadratic: -, operand quadratic: +; times a2's sign (+ for w < q)
+        const int flip = (above(t, w) ^ above(t, q)) ^ (w < q ? 0 : 1) ^ (di == 2 ? 1 : 0);
+        return flip ? -1 : 1;
+    }
+    return 0;
+}
+
+// modes below which no width is faster in triple space
+constexpr int kTriMinModes = 14;
+
+void build_triples(Graph& g, const HostGraph& hg) {
+    TriPlan& p = g.tri;
+    p.release();
+    const int m = hg.hdr.size;
+    const int64_t N = hg.hdr.n_ops;
+    if (hg.hdr.algebra != CUT_ALG_MAJORANA || m < kTriMinModes || m > 64 || hg.hdr.factor_bytes != 1) return;
+    const int64_t nq = (int64_t)m * (m - 1) / 2, nt = nq * (m - 2) / 3, n4 = nt * (m - 3) / 4;
+    if (N != nq + n4) return;
+    const int64_t len2 = 2 * (m - 2) + (int64_t)(m - 2) * (m - 3) * (m - 4) / 3, len4 = 8 * (m - 4);
+    std::unordered_map<uint64_t, int32_t> row;
+    row.reserve((size_t)N * 2);
+    const uint64_t all = m == 64 ? ~0ull : (1ull << m) - 1;
+    for (int64_t k = 0; k < N; ++k) {
+        const uint64_t L = hg.labels[k];
+        if ((L & ~all) || __builtin_popcountll(L) != (k < nq ? 2 : 4)) return;
+        if (!row.emplace(L, (int32_t)k).second) return;
+    }
+    // Every record has its sign and the common magnitude, no pair of inputs
+    // comes twice in a target, and the target has as many as the bracket: the
+    // two sets are the same.
+    const int64_t* off = hg.off[0];
+    const int32_t *ri = hg.ri[0], *rj = hg.rj[0];
+    const int8_t* rc = hg.rc[0];
+    if (off[1] == off[0]) return;
+    const int c0 = rc[off[0]] * record_sign(hg.labels[0], hg.labels[ri[off[0]]], hg.labels[rj[off[0]]]);
+    if (c0 == 0) return;
+    std::atomic<bool> good{true};
+    auto check = [&](int64_t k0, int64_t k1) {
+        for (int64_t k = k0; k < k1 && good; ++k) {
+            bool ok = off[k + 1] - off[k] == (k < nq ? len2 : len4);
+            for (int64_t e = off[k]; ok && e < off[k + 1]; ++e) {
+                ok = rc[e] == c0 * record_sign(hg.labels[k], hg.labels[ri[e]], hg.labels[rj[e]]);
+                // stored in ascending (i, j) order, each pair once
+                if (e > off[k] && (ri[e] < ri[e - 1] || (ri[e] == ri[e - 1] && rj[e] <= rj[e - 1]))) ok = false;
+            }
+            if (!ok) good = false;
+        }
+    };
+    const int nth = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+    std::vector<std::thread> th;
+    int64_t k0 = 0;
+    for (int t = 0; t < nth; ++t) {
+        // pieces of about equal record counts
+        const int64_t goal = off[N] / nth * (t + 1);
+        const int64_t k1 = t == nth - 1 ? N : std::lower_bound(off + k0, off + N, goal) - off;
+        th.emplace_back(check, k0, k1);
+        k0 = k1;
+    }
+    for (auto& t : th) t.join();
+    if (!good) return;
+    const int64_t ntau = nt + m;
+    const int64_t ntp = ntau + 16;
+    std::vector<uint32_t> tab((size_t)((m + 7) / 8 * 8 + 8) * ntp, kTriAbsent);
+    std::vector<uint64_t> tau;
+    for (int a = 0; a < m; ++a)
+        for (int b = a + 1; b < m; ++b)
+            for (int c = b + 1; c < m; ++c) tau.push_back((1ull << a) | (1ull << b) | (1ull << c));
+    for (int a = 0; a < m; ++a) tau.push_back(1ull << a);
+    for (int w = 0; w < m; ++w)
+        for (int64_t t = 0; t < ntau; ++t) {
+            if (tau[t] >> w & 1) continue;
+            tab[(size_t)w * ntp + t] =
+                (uint32_t)row.at(tau[t] | (1ull << w)) | (above(tau[t], w) ? kTriSign : 0u);
+        }
+    p.m = m;
+    p.nq = (int32_t)nq;
+    p.nt = (int32_t)nt;
+    p.ntau = (int32_t)ntau;
+    p.ntp = (int32_t)ntp;
+    p.c = (double)c0;
+    auto up = [](const void* src, size_t bytes) {
+        void* d = nullptr;
+        const hipError_t e = hipMalloc(&d, bytes);
+        if (e != hipSuccess) CUT_FAIL(CUT_E_NOMEM, "hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e));
+        HIP_CHECK(hipMemcpy(d, src, bytes, hipMemcpyHostToDevice));
+        return d;
+    };
+    p.tab = (uint32_t*)up(tab.data(), tab.size() * 4);
+    p.tmask = (uint64_t*)up(tau.data(), (size_t)nt * 8);
+    p.ok = true;
+}
+
+// ---------------------------------------------------------------- combine ----
+struct TriCombineArgs {
+    const double* p4;
+    const double* p2;
+    int32_t nstream, nq, nops, nsets, s0, w;  // sets [s0, s0 + w)
+    int64_t N, ldp;
+    double c;        // record factor, with the sign of a transposed use
+    double scale;
+    const int32_t* nsteps;
+    const int32_t* step;
+    double* y;
+    int64_t ldy;
+    int32_t accumulate;
+    int32_t stage;
+    double ds;
+    double* z;
+    double* acc;
+    void* xout;
+    int64_t ldx;
+    double* hst;
+    int64_t ldh;
+    int32_t f32;
+    // records and operands, for non-finite results
+    const int64_t* off;
+    const uint2* rec;
+    const void* A;
+    const void* B;
+    int64_t lda, ldb;
+    int32_t nred;
+    double sign;
+};
+
+// The value of row `row` straight from its records (the kernels' zero padding
+// gives NaN where an operand is not finite; the records have no such terms).
+__device__ __forceinline__ double tri_row(const TriCombineArgs& a, int64_t row, int op, int s) {
+    double v = 0.0;
+    for (int64_t e = a.off[row]; e < a.off[row + 1] && !__builtin_isnan(v); ++e) {
+        const uint2 r = a.rec[e];
+        const double f = (double)__builtin_bit_cast(float, (r.x & 0xFF000000u) | ((r.y >> 24) << 16));
+        for (int red = 0; red < a.nred; ++red) {
+            const int64_t ia = (int64_t)(r.x & 0xFFFFFFu) * a.lda + (int64_t)red * a.nsets + s;
+            const int64_t ib = (int64_t)(r.y & 0xFFFFFFu) * a.ldb + (int64_t)(red + op) * a.nsets + s;
+            const double x = a.f32 ? (double)((const float*)a.A)[ia] : ((const double*)a.A)[ia];
+            const double y = a.f32 ? (double)((const float*)a.B)[ib] : ((const double*)a.B)[ib];
+            v = __builtin_fma(f * x, y, v);
+        }
+    }
+    return a.sign * v;
+}
+
+template <int EPI>
+__device__ __forceinline__ void tri_finish(const TriCombineArgs& a, int64_t row, int op, int s, double sum) {
+    double v = a.c * sum;
+    if (__builtin_expect(!__builtin_isfinite(v), 0)) v = tri_row(a, row, op, s);
+    const int64_t col = (int64_t)op * a.nsets + s;
+    if constexpr (EPI == EPI_Y) {
+        double& o = a.y[row * a.ldy + col];
+        o = a.accumulate ? o + a.scale * v : a.scale * v;
+    } else {
+        const int64_t idx = row * a.ldx + col;
+        const double nxt = rk_combine(a.stage, a.ds, a.z, a.acc, idx, v);
+        if (a.f32) ((float*)a.xout)[idx] = (float)nxt;
+        else ((double*)a.xout)[idx] = nxt;
+        if (op == 0) a.hst[row * a.ldh + s] = nxt;
+    }
+}
+
+// Partial rows of a target added in a fixed order, then the epilogue.  Blocks
+// [0, nb2): 32 elements of the quadratic rows x 8 lanes over their streams
+// (lane l adds streams l, l + 8, ..., then the lanes in order); the others: one
+// thread per element of the quartic rows, its 4 slots in order.  Bound by the
+// memory it streams (4 partial values per element and the epilogue's state):
+// 0.29 ms at 40 modes x 320 columns, 0.94 GB of partial rows and 0.9 GB of state.
+template <int EPI>
+__global__ __launch_bounds__(256) void k_tri_combine(TriCombineArgs a, unsigned nb2) {
+    __shared__ double red[8][32];
+    const uint32_t cw = (uint32_t)a.nops * (uint32_t)a.w;
+    if (blockIdx.x < nb2) {
+        const uint64_t q = (uint64_t)blockIdx.x * 32 + threadIdx.x % 32;
+        const int l = (int)threadIdx.x / 32;
+        const bool in = q < (uint64_t)a.nq * cw;
+        const int64_t row = in ? (int64_t)(q / cw) : 0;
+        const uint32_t cc = in ? (uint32_t)(q % cw) : 0;
+        const int op = (int)(cc / (uint32_t)a.w), s = a.s0 + (int)(cc % (uint32_t)a.w);
+        const bool act = in && (a.nsteps == nullptr || a.nsteps[s] > *a.step);
+        double v = 0.0;
+        if (act) {
+            const double* p = a.p2 + row * a.ldp + (int64_t)op * a.nsets + s;
+            for (int r = l; r < a.nstream; r += 8) v += __builtin_nontemporal_load(p + (int64_t)r * a.nq * a.ldp);
+        }
+        red[l][threadIdx.x % 32] = v;
+        __syncthreads();
+        if (l != 0 || !act) return;
+        for (int k = 1; k < 8; ++k) v += red[k][threadIdx.x];
+        tri_finish<EPI>(a, row, op, s, v);
+        return;
+    }
+    const uint64_t q = (uint64_t)(blockIdx.x - nb2) * 256 + threadIdx.x;
+    if (q >= (uint64_t)(a.N - a.nq) * cw) return;
+    uint64_t r4;
+    uint32_t cc;
+    if (q < (1ull << 32)) {
+        r4 = (uint32_t)q / cw;
+        cc = (uint32_t)q - (uint32_t)r4 * cw;
+    } else {
+        r4 = q / cw;
+        cc = (uint32_t)(q % cw);
+    }
+    const int64_t row = a.nq + (int64_t)r4;
+    const int op = (int)(cc / (uint32_t)a.w), s = a.s0 + (int)(cc % (uint32_t)a.w);
+    if (a.nsteps && a.nsteps[s] <= *a.step) return;
+    const double* p = a.p4 + row * a.ldp + (int64_t)op * a.nsets + s;
+    const int64_t st = a.N * a.ldp;
+    const double v = ((__builtin_nontemporal_load(p) + __builtin_nontemporal_load(p + st)) +
+                      __builtin_nontemporal_load(p + 2 * st)) +
+                     __builtin_nontemporal_load(p + 3 * st);
+    tri_finish<EPI>(a, row, op, s, v);
+}
+
+// ----------------------------------------------------------------- launch ----
+// Shape of a launch over w sets: set quads per block (0: the one-set kernel),
+// blocks of sets, and streams of the quadratic blocks.  Everything that decides
+// the order of a sum is a function of the plan and w.
+struct TriShape {
+    int sq, chunks, tw, nwt, nbp, nstream;
+};
+
+static TriShape tri_shape(const TriPlan& p, int w) {
+    TriShape t;
+    t.sq = w <= 1 ? 0 : w <= 4 ? 1 : w <= 8 ? 2 : 4;
+    t.chunks = t.sq == 4 ? (w + 15) / 16 : 1;
+    t.tw = t.sq ? 4 / t.sq : 1;
+    // column tiles: 16 modes, 8 in the one-set kernel; tile pairs u <= v of 16
+    // rows (tw of them to a block) and one column tile
+    t.nwt = t.sq ? (p.m + 15) / 16 : (p.m + 7) / 8;
+    t.nbp = 0;
+    for (int v = 0; v < t.nwt; ++v) t.nbp += (t.sq ? v / t.tw : v / 2) + 1;
+    // about 512 blocks (two per CU; they start first and the quartic blocks fill
+    // in behind) or wavefronts of the one-set kernel, of at least 4 steps each
+    const int steps = t.sq ? (p.ntau + 3) / 4 : (p.ntau + 15) / 16;
+    const int want = (t.sq ? 512 : 1024) / (t.nbp * t.chunks);
+    t.nstream = std::max(1, std::min(want, steps / 4));
+    if (t.nstream >= 8) t.nstream &= ~7;  // whole streams per XCD
+    return t;
+}
+
+size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops) {
+    if (!g.tri.ok) return 0;
+    int streams = 1;
+    for (int w : {1, 4, 8, 16}) streams = std::max(streams, tri_shape(g.tri, w).nstream);
+    return (size_t)(4 * g.N + (int64_t)streams * g.tri.nq) * (size_t)(nops * nsets) * sizeof(double);
+}
+
+// Sets that decide a launch's shape: as wide as the segment kernel's lane
+// groups, at least min(8, nsets).
+static int tri_width(const PassArgs& a) {
+    const int w = a.s1 > 0 ? a.s1 - a.s0 : a.nsets;
+    return std::max({w, std::min(8, (int)a.nsets), (int)a.gfloor});
+}
+
+// FP64 and the compensated float modes (the sums are FP64 with exact products,
+// at least as accurate as either); 32-bit offsets into both operand arrays.
+// Every launch costs a fixed latency (two kernels, at least m / 4 dependent
+// steps of 1.6 us), which the records' E x columns have to outweigh; the
+// segment kernel is worst above 32 sets (64 lanes) and best at float with 2 to
+// 16 sets.  One action of 3 operands, us, segment kernel -> triples:
+//   above the line  14 modes x 33 sets FP64 78 -> 38, float 56 -> 35
+//                   20 x 32 FP64 84 -> 62;  24 x 8 FP64 69 -> 52
+//                   24 x 1 FP64 40 -> 31;  26 x 4 float 52 -> 52;  26 x 2 FP64 58 -> 53
+//   below it        20 x 8 FP64 0.96 of its speed, 24 x 16 float 0.97
+//                   with 5 operands  22 x 8 float 43 -> 56;  24 x 4 FP64 66 -> 71
+bool triples_usable(const Graph& g, const PassArgs& a) {
+    if (!g.tri.ok || a.precision == CUT_F32) return false;
+    const bool f64 = a.precision == CUT_F64;
+    const int w = tri_width(a);
+    const int least = w > 32 ? kTriMinModes : f64 && w > 16 ? 20 : w == 1 || w > (f64 ? 4 : 16) ? 24 : 26;
+    if (g.tri.m < least) return false;
+    if (g.N * std::max(a.lda, a.ldb) * (f64 ? 8 : 4) >= (int64_t)0x7FFFFFFF) return false;
+    return a.part_bytes >= triples_partial_bytes(g, a.nsets, a.nops);
+}
+
+void launch_triples(const Graph& g, int epi, const PassArgs& a, int nred, double sign, double* part, hipStream_t s) {
+    const TriPlan& p = g.tri;
+    const bool f32 = a.precision != CUT_F64;
+    const int s0 = a.s1 > 0 ? a.s0 : 0, s1 = a.s1 > 0 ? a.s1 : a.nsets;
+    const TriShape sh = tri_shape(p, tri_width(a));
+    const int64_t esz = f32 ? 4 : 8;
+    TriArgs t{};
+    t.tab = p.tab;
+    t.tmask = p.tmask;
+    t.m = p.m;
+    t.nt = p.nt;
+    t.ntau = p.ntau;
+    t.ntp = p.ntp;
+    t.nq = p.nq;
+    t.N = g.N;
+    t.lda = (int32_t)a.lda;
+    t.ldb = (int32_t)a.ldb;
+    t.nsets = a.nsets;
+    t.s0 = s0;
+    t.s1 = s1;
+    t.nred = nred;
+    t.nsteps = a.nsteps;
+    t.step = a.step;
+    t.ldp = (int64_t)a.nops * a.nsets;
+    t.nbp = sh.nbp;
+    t.nstream = sh.nstream;
+    t.nwt = sh.nwt;
+    // columns of the arrays: the generator side has nred column blocks, the
+    // operand side nops (nred of them in a transposed use)
+    const int64_t bytesA = ((g.N - 1) * a.lda + (int64_t)nred * a.nsets) * esz;
+    const int64_t bytesB = ((g.N - 1) * a.ldb + (int64_t)std::max((int)a.nops, nred) * a.nsets) * esz;
+    double* p4 = part;
+    double* p2 = part + 4 * g.N * t.ldp;
+    const int most = f32 ? tri_ops<float>() : tri_ops<double>();
+    for (int o = 0; o < a.nops;) {
+        const int left = a.nops - o, pieces = (left + most - 1) / most, n = (left + pieces - 1) / pieces;
+        const int64_t bo = (int64_t)o * a.nsets * esz;
+        t.A = a.A;
+        t.B = (const char*)a.B + bo;
+        t.bytesA = (uint32_t)bytesA;
+        t.bytesB = (uint32_t)(bytesB - bo);
+        t.p4 = p4 + (int64_t)o * a.nsets;
+        t.p2 = p2 + (int64_t)o * a.nsets;
+        // twice the triples per wavefront where that still leaves 4 blocks per CU
+        auto tiles = [&](int ti) { return (p.nt + 4 * ti * sh.tw - 1) / (4 * ti * sh.tw); };
+        const int ti = tri_rows(n, (int)esz) == 8 && sh.sq == 4 && (int64_t)tiles(8) * t.nwt * sh.chunks >= 1024 ? 8 : 4;
+        t.ntt = tiles(ti);
+        t.per = (t.ntt + 7) / 8;
+        dim3 grid;
+        if (sh.sq == 0) {
+            t.nb2 = t.nbp * t.nstream;
+            grid = dim3((unsigned)((t.nb2 + t.ntt * t.nwt + 3) / 4));
+        } else {
+            t.chunks = (s1 - s0 + 4 * sh.sq - 1) / (4 * sh.sq);
+            t.nb2 = t.nbp * ((t.nstream + 7) / 8) * 8 * t.chunks;
+            grid = dim3((unsigned)(t.nb2 + 8 * t.per * t.nwt * t.chunks));
+        }
+        if (f32) launch_triples_t<float>(t, n, sh.sq, ti, grid, s);
+        else launch_triples_t<double>(t, n, sh.sq, ti, grid, s);
+        o += n;
+    }
+    TriCombineArgs c{};
+    c.p4 = p4;
+    c.p2 = p2;
+    c.nstream = sh.nstream;
+    c.nq = p.nq;
+    c.nops = a.nops;
+    c.nsets = a.nsets;
+    c.s0 = s0;
+    c.w = s1 - s0;
+    c.N = g.N;
+    c.ldp = t.ldp;
+    c.c = p.c * sign;
+    c.scale = a.scale;
+    c.nsteps = a.nsteps;
+    c.step = a.step;
+    c.y = (double*)a.y;
+    c.ldy = a.ldy;
+    c.accumulate = a.accumulate;
+    c.stage = a.stage;
+    c.ds = a.ds;
+    c.z = a.z;
+    c.acc = a.acc;
+    c.xout = a.xout;
+    c.ldx = a.ldb;
+    c.hst = a.hst;
+    c.ldh = a.ldh;
+    c.f32 = f32 ? 1 : 0;
+    c.off = g.csr[0][0].off;
+    c.rec = g.csr[0][0].rec;
+    c.A = a.A;
+    c.B = a.B;
+    c.lda = a.lda;
+    c.ldb = a.ldb;
+    c.nred = nred;
+    c.sign = sign;
+    const int64_t cw = (int64_t)a.nops * c.w;
+    const unsigned nb2 = (unsigned)((p.nq * cw + 31) / 32);
+    const unsigned nb = nb2 + (unsigned)(((g.N - p.nq) * cw + 255) / 256);
+    if (epi == EPI_Y) hipLaunchKernelGGL((k_tri_combine<EPI_Y>), dim3(nb), dim3(256), 0, s, c, nb2);
+    else hipLaunchKernelGGL((k_tri_combine<EPI_RK>), dim3(nb), dim3(256), 0, s, c, nb2);
+}
+
+void launch_adjoint_x(const Graph& g, const PassArgs& a, double* part, hipStream_t s) {
+    if (part && triples_usable(g, a)) launch_triples(g, EPI_Y, a, 1, -1.0, part, s);
+    else launch_pass(MODE_BCAST, EPI_Y, a, s);
+}
+
+// out_i = sum_op L(x_op) w_op: the operand takes the generator's place and the
+// cotangent the operand's
+void launch_adjoint_eta(const Graph& g, const PassArgs& a, double* part, hipStream_t s) {
+    if (part && triples_usable(g, a)) {
+        PassArgs r = a;
+        r.A = a.B;
+        r.lda = a.ldb;
+        r.B = a.A;
+        r.ldb = a.lda;
+        r.nops = 1;
+        launch_triples(g, EPI_Y, r, a.nops, 1.0, part, s);
+    } else {
+        launch_pass(MODE_REDOPS, EPI_Y, a, s);
+    }
+}
+
+}  // namespace cut

@@ -45,6 +45,7 @@ double time_pass(Graph& g, int prec, int32_t nsets, int32_t nops, const void* et
     p.y = y;
     p.ldy = (int64_t)nops * nsets;
     p.scale = 1.0;
+    p.part_bytes = forward_partial_bytes(g, nsets, nops, prec);
     for (int w = 0; w < 2; ++w) launch_forward(g, EPI_Y, p, partials, s);  // warm
     const int reps = 3;
     HIP_CHECK(hipEventRecord(e0, s));
@@ -114,8 +115,17 @@ extern "C" cut_status cut_graph_autotune(cut_graph_t h, int64_t nsets, int64_t n
         const uint32_t shapes[] = {0u, CUT_TILE_TRIPLE_CHUNKS, CUT_TILE_NO_CHUNKS, CUT_TILE_TRIPLES,
                                    CUT_TILE_QUAD_BLOCKS, CUT_TILE_QUAD_BLOCKS | CUT_TILE_TRIPLE_CHUNKS,
                                    CUT_TILE_QUAD_BLOCKS | CUT_TILE_TRIPLES};
+        // passes in triple space have no tiling to choose: the current one stays
+        PassArgs probe{};
+        probe.precision = precision;
+        probe.nsets = (int32_t)nsets;
+        probe.nops = (int32_t)nops;
+        probe.lda = nsets;
+        probe.ldb = nops * nsets;
+        probe.part_bytes = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, precision);
+        const bool tiled = !triples_usable(g, probe);
         for (int64_t cr : crs)
-            for (uint32_t xr = 0; xr <= 1; ++xr)
+            for (uint32_t xr = 0; tiled && xr <= 1; ++xr)
                 for (uint32_t shape : shapes) {
                     if ((shape & CUT_TILE_TRIPLES) && !g.tiles.ok) continue;
                     if ((shape & CUT_TILE_TRIPLE_CHUNKS) && !g.triple_groups) continue;
@@ -153,7 +163,7 @@ extern "C" cut_status cut_graph_autotune(cut_graph_t h, int64_t nsets, int64_t n
         std::vector<Cand> bc;
         int gw = 1;
         while (gw < nsets && gw < 64) gw <<= 1;
-        for (size_t r = 0; r < std::min<size_t>(3, order.size()); ++r) {
+        for (size_t r = 0; tiled && r < std::min<size_t>(3, order.size()); ++r) {
             const Cand& c = cands[order[r]];
             const uint32_t base = c.flags & ~(3u << CUT_TILE_BCHUNK_SHIFT);
             for (uint32_t code = 1; code <= 3; ++code)
