@@ -1939,29 +1939,50 @@ __global__ void k_g2_vjp_partner(int64_t N, int32_t nsets, const int64_t* __rest
     g_h[r * ldgh + s] += acc;
 }
 
-// one wavefront per (pair a, set s); lanes stride over the pair's list
-__global__ void k_g2_vjp_pairs(int64_t npairs, int32_t nsets, const int64_t* __restrict__ poff,
-                               const int4* __restrict__ pent, const int32_t* __restrict__ pairs,
-                               const double* __restrict__ ftab, double gsign,
-                               const double* __restrict__ h, int64_t ldh,
-                               const double* __restrict__ w, const double* __restrict__ u,
-                               double* g_h, int64_t ldgh) {
-    const int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    const int64_t a = wid / nsets;
-    const int s = (int)(wid % nsets);
-    if (a >= npairs) return;
+// One block per (pair a, four sets): 256 lanes stride over the pair's list, each
+// for the four sets beside each other in a row.  The lists are few and long
+// (N / 3 to N / 4 entries for each of the m / 2 pairs), so the chain of dependent loads
+// per lane is what the launch takes: four entries are in flight at once.  The order of
+// a sum does not depend on the number of sets.  A wavefront per (pair, set) took
+// 35 us at 24 modes x 8 sets, this 13.
+constexpr int kPairSets = 4, kPairLanes = 256;
+
+__global__ __launch_bounds__(kPairSets * kPairLanes) void k_g2_vjp_pairs(
+    int64_t npairs, int32_t nsets, const int64_t* __restrict__ poff, const int4* __restrict__ pent,
+    const int32_t* __restrict__ pairs, const double* __restrict__ ftab, double gsign,
+    const double* __restrict__ h, int64_t ldh, const double* __restrict__ w, const double* __restrict__ u,
+    double* g_h, int64_t ldgh) {
+    __shared__ double red[kPairSets * kPairLanes / 64][kPairSets];
+    const int sl = (int)threadIdx.x % kPairSets, lane = (int)threadIdx.x / kPairSets;
+    const int64_t a = blockIdx.x % npairs;
+    const int s = (int)(blockIdx.x / npairs) * kPairSets + sl;
+    const int sr = s < nsets ? s : nsets - 1;  // past the last set: read, not written
     const int64_t pa = pairs[a];
-    const double eps = h[pa * ldh + s];
+    const double eps = h[pa * ldh + sr];
     double acc = 0.0;
-    for (int64_t q = poff[a] + lane; q < poff[a + 1]; q += 64) {
-        const int4 e = pent[q];
-        const double c = ftab[e.z];
-        acc += gsign * c * h[(int64_t)e.y * ldh + s] * w[(int64_t)e.x * nsets + s] -
-               2.0 * c * c * eps * u[(int64_t)e.x * nsets + s];
+    const int64_t end = poff[a + 1];
+    for (int64_t q = poff[a] + lane; q < end; q += 4 * kPairLanes) {
+        int4 e[4];
+        double c[4], hv[4], wv[4], uv[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) e[t] = pent[q + t * kPairLanes < end ? q + t * kPairLanes : q];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            c[t] = ftab[e[t].z];
+            hv[t] = h[(int64_t)e[t].y * ldh + sr];
+            wv[t] = w[(int64_t)e[t].x * nsets + sr];
+            uv[t] = u[(int64_t)e[t].x * nsets + sr];
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (q + t * kPairLanes < end) acc += gsign * c[t] * hv[t] * wv[t] - 2.0 * c[t] * c[t] * eps * uv[t];
     }
-    for (int o = 1; o < 64; o <<= 1) acc += __shfl_xor(acc, o);
-    if (lane == 0) g_h[pa * ldgh + s] += acc;
+    for (int o = kPairSets; o < 64; o <<= 1) acc += __shfl_xor(acc, o);
+    if ((threadIdx.x & 63) < kPairSets) red[threadIdx.x >> 6][sl] = acc;
+    __syncthreads();
+    if ((int)threadIdx.x >= kPairSets || s >= nsets) return;
+    for (int k = 1; k < kPairSets * kPairLanes / 64; ++k) acc += red[k][sl];
+    g_h[pa * ldgh + s] += acc;
 }
 
 // G2 directional derivative along dh (quotient rule), FP64:
@@ -2020,9 +2041,9 @@ void launch_g2_vjp(const Graph& g, double delta, int32_t nsets, const double* h,
                        g.gen_sign, delta * delta, h, ldh, gbar, ldg, w, u);
     hipLaunchKernelGGL(k_g2_vjp_partner, dim3(nb), dim3(256), 0, s, g.N, nsets, g.st_t_off, g.st_t,
                        g.pairs, g.ftab, g.gen_sign, h, ldh, w, g_h, ldgh);
-    const int64_t waves = g.npairs * nsets;
-    hipLaunchKernelGGL(k_g2_vjp_pairs, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, g.npairs,
-                       nsets, g.st_p_off, g.st_p, g.pairs, g.ftab, g.gen_sign, h, ldh, w, u, g_h, ldgh);
+    hipLaunchKernelGGL(k_g2_vjp_pairs, dim3((unsigned)(g.npairs * ((nsets + kPairSets - 1) / kPairSets))),
+                       dim3(kPairSets * kPairLanes), 0, s, g.npairs, nsets, g.st_p_off, g.st_p, g.pairs, g.ftab, g.gen_sign, h,
+                       ldh, w, u, g_h, ldgh);
 }
 
 // ------------------------------------------------------------------- G1 ----
