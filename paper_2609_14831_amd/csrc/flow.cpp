@@ -347,6 +347,28 @@ extern "C" cut_status cut_flow_integrate(cut_graph_t h, const cut_flow_params* p
         const size_t ob = outside ? flow_outside_extra(g, nsets, nops) : 0;
         char* oex = nullptr;
         FlowBufs fb = flow_bufs(g, nsets, nops, p->precision, ob, &oex);
+        int32_t* const flagp = p->nonfinite ? p->nonfinite : fb.flag;
+        auto finish = [&]() -> cut_status {
+            HIP_CHECK(hipGetLastError());
+            if (p->nonfinite) return CUT_OK;
+            int32_t flag = 0;
+            HIP_CHECK(hipMemcpyAsync(&flag, fb.flag, 4, hipMemcpyDeviceToHost, stream));
+            HIP_CHECK(hipStreamSynchronize(stream));
+            if (flag) CUT_FAIL(CUT_E_NUMERIC, "flow produced non-finite coefficients");
+            return CUT_OK;
+        };
+        // a small graph's flow is one launch (timed passes are launches of their own)
+        if (!outside && !(p->flags & CUT_FLOW_TIME_PASSES) &&
+            small_flow_usable(g, p->generator, p->precision, nsets, nops)) {
+            g.flow_nsteps_h.assign(n_steps, n_steps + nsets);
+            g.timing = cut_flow_timing{};
+            HIP_CHECK(hipMemcpyAsync(fb.nsteps, g.flow_nsteps_h.data(), nsets * 4, hipMemcpyHostToDevice, stream));
+            launch_set_scalar(flagp, 0, stream);
+            launch_flow_small(g, p->generator, p->precision, p->ds, p->delta, nsets, nops, fb.nsteps, t0, t1, z,
+                              p->ckpt_every > 0 ? ckpt : nullptr, p->ckpt_every, stream);
+            launch_finite_check(z, M, flagp, stream);
+            return finish();
+        }
         // Ragged batch: the sets run in the order of decreasing n_steps, so the
         // sets still active at step t are a prefix of length A(t) and each
         // graph pass launches over that prefix only (in pieces, set_ranges).
@@ -403,7 +425,6 @@ extern "C" cut_status cut_flow_integrate(cut_graph_t h, const cut_flow_params* p
                              stream);
         }
         launch_set_scalar(fb.step, (int32_t)t0, stream);
-        int32_t* const flagp = p->nonfinite ? p->nonfinite : fb.flag;
         launch_set_scalar(flagp, 0, stream);
         StepPlan P{&g, p->generator, p->precision, p->ds, p->delta, (int32_t)nsets, (int32_t)nops, fb, zs, {}, {}};
         for (int st = 0; st < 4; ++st) {
@@ -563,13 +584,7 @@ extern "C" cut_status cut_flow_integrate(cut_graph_t h, const cut_flow_params* p
             HIP_CHECK(hipEventRecord(gc->ev_out, run));
             HIP_CHECK(hipStreamWaitEvent(stream, gc->ev_out, 0));
         }
-        HIP_CHECK(hipGetLastError());
-        if (p->nonfinite) return CUT_OK;
-        int32_t flag = 0;
-        HIP_CHECK(hipMemcpyAsync(&flag, fb.flag, 4, hipMemcpyDeviceToHost, stream));
-        HIP_CHECK(hipStreamSynchronize(stream));
-        if (flag) CUT_FAIL(CUT_E_NUMERIC, "flow produced non-finite coefficients");
-        return CUT_OK;
+        return finish();
     } catch (const Fail& f) {
         return f.st;
     } catch (const std::bad_alloc&) {

@@ -430,6 +430,13 @@ bool triples_usable(const Graph& g, const PassArgs& a);
 void launch_adjoint_x(const Graph& g, const PassArgs& a, double* part, hipStream_t s);
 void launch_adjoint_eta(const Graph& g, const PassArgs& a, double* part, hipStream_t s);
 void launch_triples(const Graph& g, int epi, const PassArgs& a, int nred, double sign, double* part, hipStream_t s);
+// whole flow of a small graph in one launch: whether it applies, and steps
+// [t0, t1) of every set s below nsteps[s] (device), with the checkpoints of
+// those steps
+bool small_flow_usable(const Graph& g, int gen, int prec, int64_t nsets, int64_t nops);
+void launch_flow_small(const Graph& g, int gen, int prec, double ds, double delta, int64_t nsets, int64_t nops,
+                       const int32_t* nsteps, int64_t t0, int64_t t1, double* z, double* ckpt, int64_t ckpt_every,
+                       hipStream_t s);
 // rows x (nops x nsets) state: dst[r][op][s] = src[r][op][perm[s]] (inverse:
 // dst[r][op][perm[s]] = src[r][op][s])
 void launch_permute_sets(const double* src, double* dst, int64_t rows, int32_t nops, int32_t nsets,
