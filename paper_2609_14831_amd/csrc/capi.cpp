@@ -152,9 +152,10 @@ extern "C" cut_status cut_graph_apply(cut_graph_t h, int32_t which, int32_t prec
     ABI_BEGIN
     Graph& g = checked(h);
     size_t pb = 0;
-    const PassArgs p = apply_args(g, which, precision, nsets, nops, eta, lde, x, ldx, y, ldy, flags, &pb);
+    PassArgs p = apply_args(g, which, precision, nsets, nops, eta, lde, x, ldx, y, ldy, flags, &pb);
     DeviceGuard dg(g.device);
-    double* part = pb ? (double*)g.ws_part.need(pb, "cut_graph_apply (partial rows)") : nullptr;
+    double* part = nullptr;
+    if (which == CUT_GRAPH_FLOW) part = forward_part(g, p.nsets, p.nops, precision, "cut_graph_apply (partial rows)", &p.part_bytes);
     launch_forward(g, EPI_Y, p, part, (hipStream_t)stream);
     HIP_CHECK(hipGetLastError());
     ABI_END

@@ -151,8 +151,8 @@ extern "C" cut_status cut_graph_jvp(cut_graph_t hd, int32_t kind, double delta, 
     const size_t i_eta = lay.eta, i_deta = lay.deta, i_deta32 = lay.deta32, i_x32 = lay.x32, i_dx32 = lay.dx32;
     char* base = (char*)g.ws_deriv.need(cv.total, "cut_graph_jvp");
     auto at = [&](size_t i) { return (void*)(base + cv.offs[i]); };
-    const size_t pb = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, precision);
-    double* part = pb ? (double*)g.ws_part.need(pb, "cut_graph_jvp (partial rows)") : nullptr;
+    size_t pb = 0;
+    double* part = forward_part(g, (int32_t)nsets, (int32_t)nops, precision, "cut_graph_jvp (partial rows)", &pb);
 
     // eta(h) in the pass precision (rounded once for the float modes)
     void* eta = at(i_eta);
@@ -249,8 +249,8 @@ extern "C" cut_status cut_graph_vjp(cut_graph_t hd, int32_t kind, double delta, 
     const size_t i_eta = lay.eta, i_w32 = lay.w32, i_x32 = lay.x32, i_geta = lay.geta, i_tmp = lay.tmp;
     char* base = (char*)g.ws_deriv.need(cv.total, "cut_graph_vjp");
     auto at = [&](size_t i) { return (void*)(base + cv.offs[i]); };
-    const size_t pb = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, precision);
-    double* part = pb ? (double*)g.ws_part.need(pb, "cut_graph_vjp (partial rows)") : nullptr;
+    size_t pb = 0;
+    double* part = forward_part(g, (int32_t)nsets, (int32_t)nops, precision, nullptr, &pb);
 
     const void* wo = w;
     int64_t ldwo = ldw;

@@ -419,6 +419,11 @@ bool forward_set_ranges(const Graph& g, const PassArgs& a);
 // forward pass of this shape runs in)
 size_t record_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_t precision);
 
+// the partial rows of a pass outside flows: the reserved area when it holds
+// every route's, else what the records alone need (`what` names the call that
+// fails without them; null: the call runs without partial rows then)
+double* forward_part(Graph& g, int32_t nsets, int32_t nops, int32_t precision, const char* what, size_t* bytes);
+
 // triple-space passes of Majorana graphs: plan, partial rows, whether a pass
 // may take the route, and the pass  out = sign * sum_{r < nred} L(A_r) B_r
 // (A and B advance by nsets columns per r) with the epilogue of `a`

@@ -1456,6 +1456,13 @@ size_t forward_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_
     return precision == CUT_F32 ? b : std::max(b, triples_partial_bytes(g, nsets, nops));
 }
 
+double* forward_part(Graph& g, int32_t nsets, int32_t nops, int32_t precision, const char* what, size_t* bytes) {
+    *bytes = forward_partial_bytes(g, nsets, nops, precision);
+    if (*bytes <= g.ws_part.bytes) return *bytes ? (double*)g.ws_part.ptr : nullptr;
+    *bytes = what ? record_partial_bytes(g, nsets, nops, precision) : 0;
+    return *bytes ? (double*)g.ws_part.need(*bytes, what) : nullptr;
+}
+
 size_t record_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_t precision) {
     // the chunk plan's rows are always needed: a launch over part of the sets
     // runs the plain chunked form whatever the tiling

@@ -136,3 +136,23 @@ def test_operands_that_are_not_finite(L, m, nsets, nops, prec):
             assert np.array_equal(got[inf], ref[inf])
             fin = np.isfinite(ref)
             assert np.allclose(got[fin], ref[fin], rtol=1e-12, atol=1e-12)
+
+
+@pytest.mark.parametrize("m,nsets", [(14, 33), (16, 40)])
+def test_action_without_reservation(L, m, nsets):
+    """No target of these graphs is split, so the records need no partial rows:
+    an action on a handle that reserved nothing runs on them."""
+    og, ga, bound = _graph(m)
+    g = L.cut_graph_load(U.bundle_path(L, "majorana", m), 0, 0)
+    try:
+        eta = workloads.random_dense((og.N, nsets), seed=1)
+        x = workloads.random_dense((og.N, 2, nsets), seed=2)
+        y = torch.zeros((og.N, 2 * nsets), dtype=torch.float64, device=DEV)
+        L.cut_graph_apply(g, 0, L.CUT_F64, nsets, 2, torch.tensor(eta, device=DEV),
+                          torch.tensor(x.reshape(og.N, -1), device=DEV), y, reserve=False)
+        torch.cuda.synchronize()
+        S = OGr.apply(ga, np.abs(eta), np.abs(x)).reshape(og.N, -1)
+        U.assert_within(y.cpu().numpy(), OGr.apply(og, eta, x).reshape(og.N, -1), bound * S, "apply")
+        assert L.cut_graph_reserved_bytes(g) == 0
+    finally:
+        L.cut_graph_free(g)
