@@ -15,7 +15,8 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libcutgraph.so")
 BUILD = os.path.join(HERE, "_build")
 SOURCES = ["builder.cpp", "graph.cpp", "capi.cpp", "deriv.cpp", "flow.cpp", "tune.cpp", "reserve.cpp", "kernels.hip", "assemble.hip", "noalloc.hip",
-           "triples.hip", "triples_f32.hip", "triples_f64.hip", "small_flow.hip"]
+           "triples.hip", "triples_f32.hip", "triples_f64.hip", "small_flow.hip",
+           "outside_f32.hip", "outside_f64.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-x", "hip", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

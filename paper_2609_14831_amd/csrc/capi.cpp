@@ -156,7 +156,8 @@ extern "C" cut_status cut_graph_apply(cut_graph_t h, int32_t which, int32_t prec
     DeviceGuard dg(g.device);
     double* part = nullptr;
     if (which == CUT_GRAPH_FLOW) part = forward_part(g, p.nsets, p.nops, precision, "cut_graph_apply (partial rows)", &p.part_bytes);
-    launch_forward(g, EPI_Y, p, part, (hipStream_t)stream);
+    if (which == CUT_GRAPH_OUTSIDE && outside_usable(g, p)) launch_outside(g, p, (hipStream_t)stream);
+    else launch_forward(g, EPI_Y, p, part, (hipStream_t)stream);
     HIP_CHECK(hipGetLastError());
     ABI_END
 }

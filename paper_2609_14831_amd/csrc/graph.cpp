@@ -1099,6 +1099,7 @@ extern "C" cut_status cut_graph_load(const char* path, int32_t dev, uint32_t fla
         }
         if (!pb) build_tiles(*g, hg, code);
         build_triples(*g, hg);
+        build_outside(*g, hg);
         HIP_CHECK(hipDeviceSynchronize());
         HIP_CHECK(hipSetDevice(prev));
         *out = (cut_graph_t)g;

@@ -261,6 +261,13 @@ struct TriPlan {
     double c = 0.0;                           // common factor of the records
     uint32_t* tab = nullptr;                  // device [modes, padded][ntp]
     uint64_t* tmask = nullptr;                // device [nt]
+    // outside-space targets: common factor, binomials, pairs, triples and the
+    // tiles of blocks of 16, 32 and 64 rows
+    bool out_ok = false;
+    double cout = 0.0;
+    uint32_t *bin = nullptr, *pair2 = nullptr, *tri3 = nullptr;
+    int4* tasks = nullptr;
+    int32_t task0[4] = {0, 0, 0, 0};
     void release();
 };
 
@@ -430,6 +437,11 @@ double* forward_part(Graph& g, int32_t nsets, int32_t nops, int32_t precision, c
 void build_triples(Graph& g, const HostGraph& hg);
 size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops);
 bool triples_usable(const Graph& g, const PassArgs& a);
+// the same for the outside-space action (partial rows in g.ws_part)
+void build_outside(Graph& g, const HostGraph& hg);
+size_t outside_partial_bytes(const Graph& g, int64_t nsets, int64_t nops);
+bool outside_usable(const Graph& g, const PassArgs& a);
+void launch_outside(const Graph& g, const PassArgs& a, hipStream_t s);
 // the two transposed actions of E_L (a: the pass over the reverse orientation),
 // as brackets where triples_usable, with `part` as the forward pass has it
 void launch_adjoint_x(const Graph& g, const PassArgs& a, double* part, hipStream_t s);

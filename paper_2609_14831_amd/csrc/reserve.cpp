@@ -20,6 +20,16 @@ void reserve_shape(Graph& g, int64_t nsets, int64_t nops, int64_t ckpt_every, ui
     if (what & CUT_RESERVE_APPLY) small = sizeof(double) * 2 * g.N * nsets;
     if ((what & CUT_RESERVE_ADJOINT) && ckpt_every > 0)
         ws = std::max(ws, flow_ws_bytes(g, nsets, nops, CUT_F64, flow_adjoint_extra(g, nsets, nops, ckpt_every)));
+    if (what & CUT_RESERVE_APPLY) {
+        // the outside-space products' partial rows, if the memory is there: its
+        // action runs on the records without them
+        const size_t out = std::max(part, outside_partial_bytes(g, nsets, nops));
+        try {
+            g.ws_part.reserve(out);
+        } catch (const Fail&) {
+            if (out == part) throw;
+        }
+    }
     g.ws_part.reserve(part);
     g.ws_small.reserve(small);
     g.ws_deriv.reserve(deriv);

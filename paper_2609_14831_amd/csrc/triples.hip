@@ -24,9 +24,14 @@ namespace cut {
 void TriPlan::release() {
     if (tab) (void)hipFree(tab);
     if (tmask) (void)hipFree(tmask);
-    tab = nullptr;
+    if (bin) (void)hipFree(bin);
+    if (pair2) (void)hipFree(pair2);
+    if (tri3) (void)hipFree(tri3);
+    if (tasks) (void)hipFree(tasks);
+    tab = bin = pair2 = tri3 = nullptr;
     tmask = nullptr;
-    ok = false;
+    tasks = nullptr;
+    ok = out_ok = false;
 }
 
 static inline int above(uint64_t set, int q) { return __builtin_popcountll(set & ~((2ull << q) - 1)) & 1; }
@@ -57,8 +62,16 @@ static int record_sign(uint64_t K, uint64_t I, uint64_t J) {
     return 0;
 }
 
+static void* upload(const void* src, size_t bytes) {
+    void* d = nullptr;
+    const hipError_t e = hipMalloc(&d, bytes);
+    if (e != hipSuccess) CUT_FAIL(CUT_E_NOMEM, "hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e));
+    HIP_CHECK(hipMemcpy(d, src, bytes, hipMemcpyHostToDevice));
+    return d;
+}
+
 // modes below which no width is faster in triple space
-constexpr int kTriMinModes = 14;
+constexpr int kTriMinModes = 14, kOutMinModes = 18;
 
 void build_triples(Graph& g, const HostGraph& hg) {
     TriPlan& p = g.tri;
@@ -130,15 +143,8 @@ void build_triples(Graph& g, const HostGraph& hg) {
     p.ntau = (int32_t)ntau;
     p.ntp = (int32_t)ntp;
     p.c = (double)c0;
-    auto up = [](const void* src, size_t bytes) {
-        void* d = nullptr;
-        const hipError_t e = hipMalloc(&d, bytes);
-        if (e != hipSuccess) CUT_FAIL(CUT_E_NOMEM, "hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e));
-        HIP_CHECK(hipMemcpy(d, src, bytes, hipMemcpyHostToDevice));
-        return d;
-    };
-    p.tab = (uint32_t*)up(tab.data(), tab.size() * 4);
-    p.tmask = (uint64_t*)up(tau.data(), (size_t)nt * 8);
+    p.tab = (uint32_t*)upload(tab.data(), tab.size() * 4);
+    p.tmask = (uint64_t*)upload(tau.data(), (size_t)nt * 8);
     p.ok = true;
 }
 
@@ -444,6 +450,196 @@ void launch_adjoint_eta(const Graph& g, const PassArgs& a, double* part, hipStre
         launch_triples(g, EPI_Y, r, a.nops, 1.0, part, s);
     } else {
         launch_pass(MODE_REDOPS, EPI_Y, a, s);
+    }
+}
+
+// ---------------------------------------------------------------- outside ----
+// Every record of the outside-space set against the product form, one thread
+// per target: its label is the degree-6 string of its lexicographic rank, and
+// its records are 20 (m - 6) different pairs (ascending), each I = U + q, J =
+// V + q of a cut Q = U + V with factor c s(U, V) sigma(U, q) sigma(V, q).
+__global__ void k_check_outside(int64_t n, int m, const uint32_t* bin, const uint64_t* labels, const uint64_t* olabels,
+                                const int64_t* off, const uint2* rec, double c, int32_t* bad) {
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    const uint64_t Q = olabels[k];
+    bool ok = __popcll(Q) == 6 && off[k + 1] - off[k] == 20 * (m - 6) && (m == 64 || Q >> m == 0);
+    int64_t rank = n - 1;
+    int t = 6;
+    for (uint64_t x = Q; ok && x; x &= x - 1) rank -= bin[t-- * 64 + m - 1 - (__ffsll((long long)x) - 1)];
+    ok = ok && rank == k;
+    uint64_t prev = 0;
+    for (int64_t e = off[k]; ok && e < off[k + 1]; ++e) {
+        const uint2 r = rec[e];
+        const uint32_t i = r.x & 0xFFFFFFu, j = r.y & 0xFFFFFFu;
+        const uint64_t I = labels[i], J = labels[j], both = I & J, U = I & ~both, V = J & ~both;
+        const uint64_t key = (uint64_t)i << 32 | j;
+        ok = (e == off[k] || key > prev) && __popcll(I) == 4 && __popcll(J) == 4 && __popcll(both) == 1 && (U ^ V) == Q;
+        prev = key;
+        int inv = 0;  // pairs u > v
+        for (uint64_t v = V; v; v &= v - 1) inv += __popcll(U & ~((v & (~v + 1)) - 1));
+        inv += __popcll(U & ~(both - 1)) + __popcll(V & ~(both - 1));
+        const double f = (double)__builtin_bit_cast(float, (r.x & 0xFF000000u) | ((r.y >> 24) << 16));
+        ok = ok && f == ((inv & 1) ? -c : c);
+    }
+    if (!ok) *bad = 1;
+}
+
+void build_outside(Graph& g, const HostGraph& hg) {
+    TriPlan& p = g.tri;
+    const int64_t n = g.n_out;
+    const int m = p.m;
+    if (!p.ok || !g.have_outside || m < kOutMinModes || hg.off[2][1] == hg.off[2][0]) return;
+    std::vector<uint32_t> bin(7 * 64);
+    for (int k = 0; k < 7; ++k)
+        for (int c = 0; c < 64; ++c) {
+            double b = 1.0;
+            for (int i = 0; i < k; ++i) b = b * (c - i) / (i + 1);
+            bin[k * 64 + c] = c < k ? 0u : (uint32_t)std::llround(b);
+        }
+    if (n != (int64_t)bin[6 * 64 + m]) return;
+    std::vector<uint32_t> pair2, tri3;
+    for (int z = 1; z < m; ++z)
+        for (int y = 0; y < z; ++y) pair2.push_back((uint32_t)(y | z << 8));
+    for (int z = 2; z < m; ++z)
+        for (int y = 1; y < z; ++y)
+            for (int x = 0; x < y; ++x) tri3.push_back((uint32_t)(x | y << 8 | z << 16));
+    // tiles for blocks of 16, 32 and 64 rows; the three-cut ones (three times the
+    // steps) first
+    std::vector<int4> tasks;
+    for (int w = 0; w < 3; ++w) {
+        const int rt = 16 << w;
+        p.task0[w] = (int32_t)tasks.size();
+        auto add = [&](int x, int rows, int cols) {
+            for (int r = 0; r < rows; r += rt)
+                for (int j = 0; j < cols; j += kTriW) tasks.push_back(make_int4(x, r, j, rows));
+        };
+        for (int a = 0; a < m; ++a)
+            for (int e = a + 4; e < m; ++e)
+                for (int f = e + 1; f < m; ++f) add(a | e << 8 | f << 16, (e - a - 1) * (e - a - 2) / 2, e - a - 1);
+        for (int a = 0; a < m; ++a)
+            for (int e = a + 4; e < m - 1; ++e) {
+                const int d = e - a - 1;
+                add(a | e << 8 | 1 << 24, d * (d - 1) * (d - 2) / 6, m - 1 - e);
+            }
+        p.task0[w + 1] = (int32_t)tasks.size();
+    }
+    p.bin = (uint32_t*)upload(bin.data(), bin.size() * 4);
+    p.pair2 = (uint32_t*)upload(pair2.data(), pair2.size() * 4);
+    p.tri3 = (uint32_t*)upload(tri3.data(), tri3.size() * 4);
+    p.tasks = (int4*)upload(tasks.data(), tasks.size() * sizeof(int4));
+    // the factor of the first record, the others against it
+    const uint64_t Q0 = hg.out_labels[0];
+    const uint64_t I = hg.labels[hg.ri[2][0]], J = hg.labels[hg.rj[2][0]], both = I & J, U = I & ~both, V = J & ~both;
+    int inv = 0;
+    for (uint64_t v = V; v; v &= v - 1) inv += __builtin_popcountll(U & ~((v & (~v + 1)) - 1));
+    inv += __builtin_popcountll(U & ~(both - 1)) + __builtin_popcountll(V & ~(both - 1));
+    if ((U ^ V) != Q0 || __builtin_popcountll(both) != 1) return;
+    p.cout = (inv & 1) ? -(double)hg.rc[2][0] : (double)hg.rc[2][0];
+    uint64_t* dl = (uint64_t*)upload(hg.labels, (size_t)g.N * 8);
+    uint64_t* dol = (uint64_t*)upload(hg.out_labels, (size_t)n * 8);
+    int32_t bad = 0;
+    int32_t* dbad = (int32_t*)upload(&bad, 4);
+    hipLaunchKernelGGL(k_check_outside, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, 0, n, m, p.bin, dl, dol,
+                       g.csr[2][0].off, g.csr[2][0].rec, p.cout, dbad);
+    const hipError_t e = hipMemcpy(&bad, dbad, 4, hipMemcpyDeviceToHost);
+    (void)hipFree(dl);
+    (void)hipFree(dol);
+    (void)hipFree(dbad);
+    HIP_CHECK(e);
+    p.out_ok = p.cout != 0.0 && !bad;
+}
+
+// Partial rows of the outside-space products: 4 per target, for as many operands at a
+// time as fit 2 GiB (0: not even one does).
+static size_t outside_one(const Graph& g, int64_t nsets) { return (size_t)(4 * g.n_out * nsets) * sizeof(double); }
+
+size_t outside_partial_bytes(const Graph& g, int64_t nsets, int64_t nops) {
+    constexpr size_t kCap = (size_t)2 << 30;
+    if (!g.tri.out_ok) return 0;
+    const size_t one = outside_one(g, nsets);
+    return one > kCap ? 0 : one * std::min<size_t>((size_t)nops, kCap / one);
+}
+
+// The products do 1.9 (24 modes) to 4 (16) times the records' operations on the
+// padding of their tiles, and every tile is a chain of 3 m / 4 steps; the records are
+// streamed once per column group of the segment kernel.  One action, us,
+// segment kernel -> products:
+//   above the line  24 modes, 8 sets x 3 operands FP64 835 -> 323, 16 x 3 float 1.5 times faster
+//                   22 x 1 x 3 FP64 1.2, 20 x 4 x 3 float 1.1, 18 x 8 x 3 FP64 1.07 times
+//   below it        20 x 1 x 3 FP64 0.89 of its speed, 18 x 8 x 3 float 0.85, 16 x 8 x 3 FP64 0.76
+bool outside_usable(const Graph& g, const PassArgs& a) {
+    const int least = a.nsets == 1 ? 22 : a.precision == CUT_F64 && a.nsets > 4 ? 18 : 20;
+    if (!g.tri.out_ok || g.tri.m < least || a.precision == CUT_F32 || g.ws_part.bytes < outside_one(g, a.nsets)) return false;
+    const int64_t esz = a.precision == CUT_F64 ? 8 : 4;
+    return g.N * std::max(a.lda, a.ldb) * esz < (int64_t)0x7FFFFFFF;
+}
+
+void launch_outside(const Graph& g, const PassArgs& a, hipStream_t s) {
+    const TriPlan& p = g.tri;
+    const bool f32 = a.precision != CUT_F64;
+    const int64_t esz = f32 ? 4 : 8;
+    const int sq = a.nsets <= 4 ? 1 : a.nsets <= 8 ? 2 : 4, w = sq == 4 ? 0 : sq == 2 ? 1 : 2;
+    const int chunks = (a.nsets + 4 * sq - 1) / (4 * sq), ntask = p.task0[w + 1] - p.task0[w];
+    const int fit = (int)std::min<size_t>((size_t)a.nops, g.ws_part.bytes / outside_one(g, a.nsets));
+    const int most = f32 ? tri_ops<float>() : tri_ops<double>();
+    const int64_t bytesA = ((g.N - 1) * a.lda + a.nsets) * esz;
+    const int64_t bytesB = ((g.N - 1) * a.ldb + (int64_t)a.nops * a.nsets) * esz;
+    for (int o = 0; o < a.nops; o += fit) {
+        const int nops = std::min(fit, (int)a.nops - o);
+        TriArgs t{};
+        t.tab = p.tab;
+        t.m = p.m;
+        t.nt = p.nt;
+        t.ntau = p.ntau;
+        t.ntp = p.ntp;
+        t.N = g.n_out;
+        t.lda = (int32_t)a.lda;
+        t.ldb = (int32_t)a.ldb;
+        t.nsets = a.nsets;
+        t.s1 = a.nsets;
+        t.nred = 1;
+        t.ldp = (int64_t)nops * a.nsets;
+        t.chunks = chunks;
+        t.tasks = p.tasks + p.task0[w];
+        t.bin = p.bin;
+        t.pair2 = p.pair2;
+        t.tri3 = p.tri3;
+        t.A = a.A;
+        t.bytesA = (uint32_t)bytesA;
+        for (int q = 0; q < nops;) {
+            const int left = nops - q, pieces = (left + most - 1) / most, k = (left + pieces - 1) / pieces;
+            const int64_t bo = (int64_t)(o + q) * a.nsets * esz;
+            t.B = (const char*)a.B + bo;
+            t.bytesB = (uint32_t)(bytesB - bo);
+            t.p4 = (double*)g.ws_part.ptr + (int64_t)q * a.nsets;
+            const dim3 grid((unsigned)((int64_t)ntask * chunks));
+            if (f32) launch_outside_t<float>(t, k, sq, grid, s);
+            else launch_outside_t<double>(t, k, sq, grid, s);
+            q += k;
+        }
+        TriCombineArgs c{};
+        c.p4 = (const double*)g.ws_part.ptr;
+        c.nops = nops;
+        c.nsets = a.nsets;
+        c.w = a.nsets;
+        c.N = g.n_out;
+        c.ldp = t.ldp;
+        c.c = p.cout;
+        c.scale = a.scale;
+        c.y = (double*)a.y + (int64_t)o * a.nsets;
+        c.ldy = a.ldy;
+        c.accumulate = a.accumulate;
+        c.f32 = f32 ? 1 : 0;
+        c.off = g.csr[2][0].off;
+        c.rec = g.csr[2][0].rec;
+        c.A = a.A;
+        c.B = (const char*)a.B + (int64_t)o * a.nsets * esz;
+        c.lda = a.lda;
+        c.ldb = a.ldb;
+        c.nred = 1;
+        c.sign = 1.0;
+        hipLaunchKernelGGL((k_tri_combine<EPI_Y>), dim3((unsigned)((g.n_out * t.ldp + 255) / 256)), dim3(256), 0, s, c, 0u);
     }
 }
 

@@ -53,7 +53,28 @@ struct TriArgs {
     int32_t nb2, nstream, nbp;  // quadratic blocks, streams (ranges of t), mode tile pairs
     int32_t nwt, ntt, per;      // quartic blocks: mode tiles, triple tiles, triple tiles per XCD
     int32_t chunks;             // blocks of sets
+    const int4* tasks;          // outside-space targets: tiles (see OutTask)
+    const uint32_t* bin;        // [k][64] binomials C(n, k)
+    const uint32_t* pair2;      // colexicographic pairs y | z << 8
+    const uint32_t* tri3;       // colexicographic triples x | y << 8 | z << 16
 };
+
+// Targets of a tile.  The two of E_L; and of E_C, for the degree-6 target Q:
+//   y[Q] = c sum over its 10 cuts Q = U + V into triples
+//          s(U, V) sum_q (e4[U, q] x4[V, q] - x4[U, q] e4[V, q]),
+// s the sign of sorting U V.  With a the lowest and e < f the highest modes of
+// Q fixed, L = {x, y, z} the rest (all between a and e), nine cuts have a
+// single mode of L on one side: for each of
+//   {x, a, e | y, z, f}   {x, a, f | y, z, e}   {x, e, f | y, z, a}
+// the sums over q are a product of rows x and pairs yz, and the three are
+// summed as one product over (cut, q): L receives it at (x; yz), (y; xz) and
+// (z; xy), into partial rows 1 .. 3.  The tenth cut, L | a e f, is a product of
+// the triples L and the modes f for fixed a and e, into partial row 0.
+enum TriKind { TRI_QUARTIC, TRI_QUADRATIC, TRI_OUT3, TRI_OUT1 };
+
+// A tile of outside-space targets: .x = a | e << 8 | f << 16 | (OUT1 ? 1 << 24 : 0),
+// .y = first row (pair or triple), .z = first column, .w = rows of the product.
+typedef int4 OutTask;
 
 constexpr uint32_t kTriRow = 0xFFFFFFu, kTriSign = 0x80000000u, kTriAbsent = 0x40000000u;
 constexpr uint32_t kTriOut = 0x80000000u;  // past every array (below 2 GiB)
@@ -125,16 +146,23 @@ struct TriTile {
     int r0, j0, kb, ke, stream;  // first row of R and S, range of k
     int set0;                    // first set of the block
     int sq, tw, u0;              // this wavefront: set quad, row tile, its first row
+    int a, e, f, rows;           // outside-space tiles: fixed modes, rows of the product
 };
+
+// lexicographic rank of the triple i < j < k
+__device__ __forceinline__ uint32_t tri_rank(const TriArgs& a, int i, int j, int k) {
+    return (uint32_t)(a.nt - 1) - a.bin[3 * 64 + a.m - 1 - i] - a.bin[2 * 64 + a.m - 1 - j] - (uint32_t)(a.m - 1 - k);
+}
 
 // NJ: column tiles of 4 that exist (0: this wavefront has no sums and only
 // stages); DIAG: only the tiles of the pairs u <= v.  Both are fixed at compile
 // time: a branch around each product costs more than the product.
-template <int NOPS, int SQ, int TI, class T, bool QUAD, int NJ, bool DIAG>
+template <int NOPS, int SQ, int TI, class T, TriKind KIND, int NJ, bool DIAG>
 __device__ __forceinline__ void tri_tile(const TriArgs& a, T* lds, const TriTile& w) {
     constexpr int C = NOPS + 1, SETS = 4 * SQ, TW = 4 / SQ, RS = TI / 4;
     constexpr int STRIDE = tri_stride<C, SETS, T>(), RROWS = TW * TI * 16;
     constexpr int NI = DIAG && NJ < TI ? NJ : TI;
+    constexpr bool QUAD = KIND == TRI_QUADRATIC, OUT = KIND == TRI_OUT3 || KIND == TRI_OUT1;
     const int m = a.m, nt = a.nt, ntp = a.ntp;
     const int lane = threadIdx.x & 63;
     // staging: slot h of thread t holds the 4 sets 4 (t % SQ) .. of one (row, k)
@@ -144,20 +172,21 @@ __device__ __forceinline__ void tri_tile(const TriArgs& a, T* lds, const TriTile
     const uint32_t lo = (uint32_t)(w.set0 + 4 * p4) * (uint32_t)sizeof(T);
     const int32_t cstep = a.nsets * (int32_t)sizeof(T);
     uint32_t ie[RS + 1];  // table index of each slot's entry at k = 0, slot RS: S
-    const uint32_t kr = QUAD ? 1u : (uint32_t)ntp;  // its step per k
-#pragma unroll
-    for (int h = 0; h < RS; ++h) {
-        const int x = w.r0 + (h * (64 * TW) + rk) / 16 * 4 + ((rk >> 2) & 3), k = rk & 3;
-        if constexpr (QUAD) ie[h] = (uint32_t)(x < m ? x : m) * (uint32_t)ntp + (uint32_t)k;  // row m: absent
-        else ie[h] = (uint32_t)(x < nt ? x : nt - 1) + (uint32_t)k * (uint32_t)ntp;
-    }
+    const uint32_t kr = QUAD ? 1u : (uint32_t)ntp, ks = OUT ? (uint32_t)ntp : 1u;  // its step per k
     const bool sact = rk < 64;  // S slots: 16 rows x 4 k
     // LDS row (tile, k, row): neighbouring threads take neighbouring k, whose
     // rows lie 16 banks apart
     const int lr = rk / 16 * 16 + (rk & 3) * 4 + ((rk >> 2) & 3);
-    {
-        const int x = w.j0 + (rk & 63) / 16 * 4 + ((rk >> 2) & 3), k = rk & 3;
-        ie[RS] = (uint32_t)(x < m ? x : m) * (uint32_t)ntp + (uint32_t)(QUAD ? k : nt + k);
+    const int rx = w.r0 + rk / 16 * 4 + ((rk >> 2) & 3);            // slot 0's row of R, slot h 16 TW further
+    const int sx = w.j0 + (rk & 63) / 16 * 4 + ((rk >> 2) & 3), sk = rk & 3;
+    if constexpr (!OUT) {
+#pragma unroll
+        for (int h = 0; h < RS; ++h) {
+            const int x = rx + h * (16 * TW);
+            if constexpr (QUAD) ie[h] = (uint32_t)(x < m ? x : m) * (uint32_t)ntp + (uint32_t)sk;  // row m: absent
+            else ie[h] = (uint32_t)(x < nt ? x : nt - 1) + (uint32_t)sk * (uint32_t)ntp;
+        }
+        ie[RS] = (uint32_t)(sx < m ? sx : m) * (uint32_t)ntp + (uint32_t)(QUAD ? sk : nt + sk);
     }
     const int js = lane & 3, bs = (lane >> 2) & 3, is = lane >> 4;
     double acc[TI][NJ > 0 ? NJ : 1][NOPS];
@@ -168,8 +197,40 @@ __device__ __forceinline__ void tri_tile(const TriArgs& a, T* lds, const TriTile
 #pragma unroll
             for (int op = 0; op < NOPS; ++op) acc[i][j][op] = 0.0;
 
-    for (int red = 0; red < a.nred; ++red) {
-        const uint32_t ro = (uint32_t)red * (uint32_t)cstep;
+    // operand columns summed over; outside-space tiles: the three cuts
+    const int nred = KIND == TRI_OUT3 ? 3 : KIND == TRI_OUT1 ? 1 : a.nred;
+    for (int red = 0; red < nred; ++red) {
+        const uint32_t ro = OUT ? 0u : (uint32_t)red * (uint32_t)cstep;
+        // the first cut's sign against the others' (13, 8 and 4 + #{y, z > x}
+        // inversions of V U), on its rows R
+        const uint32_t flip = KIND == TRI_OUT3 && red == 0 ? kTriSign : 0u;
+        if constexpr (OUT) {
+            // triples of the slots' rows; past the last row the padding columns, absent
+#pragma unroll
+            for (int h = 0; h < RS; ++h) {
+                const int x = rx + h * (16 * TW);
+                uint32_t t = (uint32_t)a.ntau;
+                if (x < w.rows) {
+                    if constexpr (KIND == TRI_OUT1) {
+                        const uint32_t l = a.tri3[x];
+                        t = tri_rank(a, w.a + 1 + (int)(l & 255), w.a + 1 + (int)(l >> 8 & 255), w.a + 1 + (int)(l >> 16));
+                    } else {
+                        const uint32_t l = a.pair2[x];
+                        const int y = w.a + 1 + (int)(l & 255), z = w.a + 1 + (int)(l >> 8);
+                        t = red == 2 ? tri_rank(a, w.a, y, z) : tri_rank(a, y, z, red ? w.e : w.f);
+                    }
+                }
+                ie[h] = (uint32_t)sk * (uint32_t)ntp + t;
+            }
+            uint32_t t = (uint32_t)a.ntau;
+            if constexpr (KIND == TRI_OUT1) {
+                if (w.e + 1 + sx < m) t = tri_rank(a, w.a, w.e, w.e + 1 + sx);
+            } else {
+                const int x = w.a + 1 + sx;
+                if (x < w.e) t = red == 2 ? tri_rank(a, x, w.e, w.f) : tri_rank(a, w.a, x, red ? w.f : w.e);
+            }
+            ie[RS] = (uint32_t)sk * (uint32_t)ntp + t;
+        }
         const auto rsA = row_rsrc((const char*)a.A + ro, (int64_t)(a.bytesA - ro));
         const auto rsB = row_rsrc((const char*)a.B + ro, (int64_t)(a.bytesB - ro));
         uint32_t e[RS + 1], sg[RS + 1];
@@ -177,7 +238,7 @@ __device__ __forceinline__ void tri_tile(const TriArgs& a, T* lds, const TriTile
         auto entries = [&](int k) {
 #pragma unroll
             for (int h = 0; h < RS; ++h) e[h] = buf_load<uint32_t>(rsTab, (ie[h] + (uint32_t)k * kr) * 4u, 0);
-            e[RS] = buf_load<uint32_t>(rsTab, (ie[RS] + (uint32_t)k) * 4u, 0);
+            e[RS] = buf_load<uint32_t>(rsTab, (ie[RS] + (uint32_t)k * ks) * 4u, 0);
         };
         auto load = [&]() {
 #pragma unroll
@@ -185,7 +246,7 @@ __device__ __forceinline__ void tri_tile(const TriArgs& a, T* lds, const TriTile
                 // where the block has fewer than 256 slots of S the others load nothing
                 const bool out = (e[h] & kTriAbsent) != 0 || (h == RS && SQ < 4 && !sact);
                 // a2[w, q]: + for w < q, where sigma({q}, w) is -
-                sg[h] = (!QUAD && h == RS ? ~e[h] : e[h]) & kTriSign;
+                sg[h] = ((KIND == TRI_QUARTIC && h == RS ? ~e[h] : e[h]) & kTriSign) ^ (h < RS ? flip : 0u);
                 const uint32_t va = (out ? kTriOut : (e[h] & kTriRow) * lda_b) + lo;
                 const uint32_t vb = (out ? kTriOut : (e[h] & kTriRow) * ldb_b) + lo;
 #pragma unroll
@@ -251,6 +312,47 @@ __device__ __forceinline__ void tri_tile(const TriArgs& a, T* lds, const TriTile
     if constexpr (NJ > 0) {
         const int s = w.set0 + 4 * w.sq + bs;
         if (s >= a.s1 || (a.nsteps != nullptr && a.nsteps[s] <= *a.step)) return;
+        if constexpr (OUT) {
+            auto bin = [&](int k, int c) { return a.bin[k * 64 + m - 1 - c]; };
+            // lexicographic rank of the target, less its terms of L (OUT1: and of f)
+            const uint32_t base = (uint32_t)(a.N - 1) - bin(6, w.a) - bin(2, w.e);
+            uint32_t l[NI];
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int x = w.u0 + 4 * i + is;
+                l[i] = x >= w.rows ? 0u : KIND == TRI_OUT1 ? a.tri3[x] : a.pair2[x];
+            }
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                if (w.u0 + 4 * i + is >= w.rows) continue;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    int c0 = w.a + 1 + (int)(l[i] & 255), c1 = w.a + 1 + (int)(l[i] >> 8 & 255), c2, f, slot;
+                    uint32_t sgn = 0;
+                    if constexpr (KIND == TRI_OUT1) {
+                        c2 = w.a + 1 + (int)(l[i] >> 16);
+                        f = w.e + 1 + w.j0 + 4 * j + js;
+                        if (f >= m) continue;
+                        slot = 0;
+                        sgn = kTriSign;  // 3 inversions of L a e f
+                    } else {
+                        const int x = w.a + 1 + w.j0 + 4 * j + js;
+                        if (x >= w.e || x == c0 || x == c1) continue;
+                        f = w.f;
+                        slot = 1 + (x < c1) + (x < c0);
+                        if (slot == 2) sgn = kTriSign;
+                        c2 = c1 > x ? c1 : x;
+                        c1 = x < c0 ? c0 : x < c1 ? x : c1;
+                        c0 = x < c0 ? x : c0;
+                    }
+                    const uint32_t row = base - bin(1, f) - bin(5, c0) - bin(4, c1) - bin(3, c2);
+                    double* p = a.p4 + ((int64_t)slot * a.N + row) * a.ldp + s;
+#pragma unroll
+                    for (int op = 0; op < NOPS; ++op) p[(int64_t)op * a.nsets] = tri_signed<double>(acc[i][j][op], sgn);
+                }
+            }
+            return;
+        }
         // every target's table entry before the first store: a load behind the
         // stores would wait for them
         uint32_t et[NI][NJ];
@@ -328,14 +430,51 @@ __device__ __forceinline__ void tri_block(const TriArgs& a, T* lds, int b) {
     w.u0 = w.r0 + w.tw * (4 * TI);
     const bool half = a.m - w.j0 <= 8;  // no more than two column tiles exist
     const bool work = w.set0 + 4 * w.sq < a.s1 && (QUAD ? (w.u0 <= w.j0 && w.u0 < a.m) : w.u0 < a.nt);
-    if (!work) tri_tile<NOPS, SQ, TI, T, QUAD, 0, false>(a, lds, w);
+    constexpr TriKind KIND = QUAD ? TRI_QUADRATIC : TRI_QUARTIC;
+    if (!work) tri_tile<NOPS, SQ, TI, T, KIND, 0, false>(a, lds, w);
     else if (QUAD && w.u0 == w.j0) {
-        if (half) tri_tile<NOPS, SQ, TI, T, QUAD, 2, QUAD>(a, lds, w);
-        else tri_tile<NOPS, SQ, TI, T, QUAD, 4, QUAD>(a, lds, w);
+        if (half) tri_tile<NOPS, SQ, TI, T, KIND, 2, QUAD>(a, lds, w);
+        else tri_tile<NOPS, SQ, TI, T, KIND, 4, QUAD>(a, lds, w);
     } else {
-        if (half) tri_tile<NOPS, SQ, TI, T, QUAD, 2, false>(a, lds, w);
-        else tri_tile<NOPS, SQ, TI, T, QUAD, 4, false>(a, lds, w);
+        if (half) tri_tile<NOPS, SQ, TI, T, KIND, 2, false>(a, lds, w);
+        else tri_tile<NOPS, SQ, TI, T, KIND, 4, false>(a, lds, w);
     }
+}
+
+// one tile of outside-space targets, for the set block b % chunks
+template <int NOPS, int SQ, class T, TriKind KIND>
+__device__ __forceinline__ void tri_outside(const TriArgs& a, T* lds, const OutTask& t, int chunk) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    TriTile w;
+    w.sq = wave % SQ;
+    w.tw = wave / SQ;
+    w.stream = 0;
+    w.set0 = a.s0 + chunk * (4 * SQ);
+    w.a = t.x & 255;
+    w.e = t.x >> 8 & 255;
+    w.f = t.x >> 16 & 255;
+    w.rows = t.w;
+    w.r0 = t.y;
+    w.j0 = t.z;
+    w.kb = 0;
+    w.ke = a.m;
+    w.u0 = w.r0 + w.tw * 16;
+    const int cols = (KIND == TRI_OUT1 ? a.m : w.e) - (KIND == TRI_OUT1 ? w.e : w.a) - 1;
+    if (w.set0 + 4 * w.sq >= a.s1 || w.u0 >= w.rows) tri_tile<NOPS, SQ, 4, T, KIND, 0, false>(a, lds, w);
+    else if (cols - w.j0 <= 8) tri_tile<NOPS, SQ, 4, T, KIND, 2, false>(a, lds, w);
+    else tri_tile<NOPS, SQ, 4, T, KIND, 4, false>(a, lds, w);
+}
+
+// Bound like the tiles of E_L by the latency of a step, and by padding: 0.54 of
+// the 16 x 16 tiles' elements are targets at 24 modes, 0.65 at 32.  24 modes, 8
+// sets x 3 FP64 operands: 0.30 ms, the products alone 0.10; the combine 0.02.
+template <int NOPS, int SQ, class T>
+__global__ __launch_bounds__(256, 2) void k_outside(TriArgs a) {
+    extern __shared__ __align__(16) unsigned char tri_lds[];
+    const int chunk = (int)blockIdx.x % a.chunks;
+    const OutTask t = a.tasks[blockIdx.x / a.chunks];
+    if (t.x >> 24) tri_outside<NOPS, SQ, T, TRI_OUT1>(a, reinterpret_cast<T*>(tri_lds), t, chunk);
+    else tri_outside<NOPS, SQ, T, TRI_OUT3>(a, reinterpret_cast<T*>(tri_lds), t, chunk);
 }
 
 template <int NOPS, int SQ, int TI, class T>
@@ -520,5 +659,19 @@ static void launch_triples_n(const TriArgs& a, int sq, int ti, dim3 grid, hipStr
 // ti: row tiles of 4 per wavefront of the quartic blocks
 template <class T>
 void launch_triples_t(const TriArgs& a, int nops, int sq, int ti, dim3 grid, hipStream_t s);
+
+// one launch over `nops` operand columns of the outside-space tiles
+template <int NOPS, class T>
+static void launch_outside_n(const TriArgs& a, int sq, dim3 grid, hipStream_t s) {
+    auto lds = [](int q) -> size_t {
+        const int stride = q == 4 ? tri_stride<NOPS + 1, 16, T>() : q == 2 ? tri_stride<NOPS + 1, 8, T>() : tri_stride<NOPS + 1, 4, T>();
+        return (size_t)(4 / q * 64 + 64) * stride * sizeof(T);
+    };
+    if (sq == 4) hipLaunchKernelGGL((k_outside<NOPS, 4, T>), grid, dim3(256), lds(4), s, a);
+    else if (sq == 2) hipLaunchKernelGGL((k_outside<NOPS, 2, T>), grid, dim3(256), lds(2), s, a);
+    else hipLaunchKernelGGL((k_outside<NOPS, 1, T>), grid, dim3(256), lds(1), s, a);
+}
+template <class T>
+void launch_outside_t(const TriArgs& a, int nops, int sq, dim3 grid, hipStream_t s);
 
 }  // namespace cut
