@@ -147,7 +147,7 @@ Graph::~Graph() {
 // XCD remapping, the target range is cut into 8 contiguous pieces of equal
 // record count (one per XCD, so neighbouring targets share one L2), each piece
 // lists its long tasks first; shorter lists are padded with empty tasks.
-static std::vector<Task> plan_tasks(const Graph& g, const std::vector<int64_t>& off, int64_t nseg, int64_t* per_xcd);
+static std::vector<Task> plan_tasks(const Graph& g, const std::vector<int64_t>& off, int64_t nseg, int64_t* per_xcd, int64_t split);
 
 static void upload_tasks(const std::vector<Task>& all, Task** dst, int64_t* n) {
     dev_free(*dst);
@@ -355,6 +355,13 @@ static void build_qb_tiling(Graph& g, const DevCSR& c) {
     q.active = true;
 }
 
+// Records of a complex-record target of E_L above which it is split over a
+// workgroup: a wavefront's chain of 1024 records outlasts the launch's other
+// work where there are few targets.  10 steps of 8 operators, us, 1024 -> 512:
+// modes x degree 4 x 4 (1980 targets) 1531 -> 1420, 3 x 4 852 -> 802, 2 x 4 676 ->
+// 641; 256 gains no more and costs 7 % with 4 operators on 336 targets.
+constexpr int64_t kComplexSplit = 512;
+
 void build_tasks(Graph& g, DevCSR& c) {
     ++g.tiling_gen;
     c.per_xcd = 0;
@@ -362,14 +369,15 @@ void build_tasks(Graph& g, DevCSR& c) {
         upload_tasks({}, &c.tasks, &c.ntasks);
         return;
     }
-    upload_tasks(plan_tasks(g, c.off_h, c.nseg, &c.per_xcd), &c.tasks, &c.ntasks);
+    const int64_t split = &c == &g.cxs[0] ? std::min(g.long_records, kComplexSplit) : g.long_records;
+    upload_tasks(plan_tasks(g, c.off_h, c.nseg, &c.per_xcd, split), &c.tasks, &c.ntasks);
     if (&c == &g.csr[0][0]) {
         build_chunks(g, c, c.cp, false);
         build_qb_tiling(g, c);
     }
     if (&c == &g.csr[0][0] && g.tiles.ok) {
         g.tiles.res_per_xcd = 0;
-        upload_tasks(plan_tasks(g, c.off_h, g.tiles.nres, &g.tiles.res_per_xcd), &g.tiles.res_tasks,
+        upload_tasks(plan_tasks(g, c.off_h, g.tiles.nres, &g.tiles.res_per_xcd, g.long_records), &g.tiles.res_tasks,
                      &g.tiles.nres_tasks);
     }
 }
@@ -394,18 +402,19 @@ uint32_t tiling_flags(const Graph& g) {
            (g.use_quadblocks ? CUT_TILE_QUAD_BLOCKS : 0u) | ((uint32_t)g.bchunk << CUT_TILE_BCHUNK_SHIFT);
 }
 
-static std::vector<Task> plan_tasks(const Graph& g, const std::vector<int64_t>& off, int64_t nseg, int64_t* per_xcd) {
+static std::vector<Task> plan_tasks(const Graph& g, const std::vector<int64_t>& off, int64_t nseg, int64_t* per_xcd,
+                                    int64_t split) {
     auto plan = [&](int64_t b, int64_t e, std::vector<Task>& out) {
         std::vector<Task> shorts;
         for (int64_t k = b; k < e;) {
-            if (off[k + 1] - off[k] > g.long_records) {
+            if (off[k + 1] - off[k] > split) {
                 out.push_back({(int32_t)k, -1});
                 ++k;
                 continue;
             }
             int64_t k0 = k;
             int n = 0;
-            while (k < e && n < 4 && off[k + 1] - off[k] <= g.long_records) {
+            while (k < e && n < 4 && off[k + 1] - off[k] <= split) {
                 ++k;
                 ++n;
             }
