@@ -4,8 +4,7 @@
 Workload: the batched coflow on the 2n = 40 Majorana-string graph (N = 92,170
 strings, E = 39,539,760 records): 64 coefficient sets (mass-scaling sweep) x
 (H + 4 quadratic observables) = 320 operand columns, G2 generator, classic RK4
-at ds = 5e-3, float-operand graph passes with compensated accumulation, FP64 RK
-state, one hipGraph launch per RK step.  A step = one RK4 step of the whole
+at ds = 5e-3, graph passes with float operands summed in FP64, FP64 RK state, one hipGraph launch per RK step.  A step = one RK4 step of the whole
 batch (4 x {generator, graph pass with the fused stage update}).
 
 Printed (one JSON line): contributions x batch / s over the timed steps; the
@@ -73,26 +72,20 @@ def pass_bytes(N, E, nsets, nops, prec_bytes):
             + N * cols * (8 + 14) + N * cols * prec_bytes + N * nsets * 8)
 
 
-def pass_kernels(flags: int) -> str:
-    """The kernels of one fused flow pass at 64 sets x 5 operands in a tiling."""
-    parts = []
-    if flags & 16:
-        parts.append("k_qblock<5,prec> (quadratic-target blocks)")
-    if flags & 2:
-        parts.append("k_tile64<5,prec> (shared-triple tiles of the quartic targets)")
-    G = 64 >> ((flags >> 5) & 3)   # the B-chunk: lanes per record of the segment kernel
-    parts.append(f"k_pass<{G},5,prec,0,2> (" + ("remaining targets" if flags & 18 else "every target") +
-                 (", unchunked" if flags & 4 else ", long ones in chunks") + ")")
-    if not flags & 4 or flags & 18:
-        parts.append("k_chunk_combine<5,prec,2> (partial rows + RK4 stage epilogue)")
-    return "fused graph pass with RK4 stage epilogue: " + " + ".join(parts)
+def pass_kernels(precision: str) -> str:
+    """The kernels of one fused flow pass at 64 sets x 5 operands."""
+    if precision == "f32":
+        return "fused graph pass with RK4 stage epilogue: k_pass<G,5,3,0,2> in the chosen tiling"
+    T = "double" if precision == "f64" else "float"
+    return (f"fused graph pass with RK4 stage epilogue: k_triples<{3 if T == 'double' else 5},4,4,{T}> (the bracket as "
+            "FP64 matrix products over triples of modes) + k_tri_combine<2> (partial rows + RK4 stage epilogue)")
 
 
-KERNEL_SOURCES = ("kernels.hip",)
+KERNEL_SOURCES = ("triples_kernel.h", "triples.hip", "device.h")
 
 
 def kernel_digest() -> str:
-    """sha256 over the sources of the segment-pass kernels, in a fixed order."""
+    """sha256 over the sources of the fused pass's kernels, in a fixed order."""
     import hashlib
     h = hashlib.sha256()
     for name in KERNEL_SOURCES:
@@ -676,8 +669,8 @@ def main():
                                   f"{nsets} sets x {nops} operands = {nsets * nops} columns, ragged "
                                   f"s_max in [2,20], ds={w.ds}, G2 generator (delta={w.delta}), RK4, "
                                   f"one hipGraph per step",
-                      "precision": {"f32c": "float operands and products, compensated (two-product + "
-                                            "two-sum) accumulation, FP64 result and RK state",
+                      "precision": {"f32c": "compensated float mode: float operands, products and sums in FP64 at "
+                                            "this size, FP64 result and RK state",
                                     "f32x": "float operands, products and sums in FP64, FP64 RK state",
                                     "f64": "FP64 throughout", "f32": "plain float sums"}[args.precision],
                       "graph_compile_s": desc["build_seconds"], "graph_load_s": load_s,
@@ -706,7 +699,7 @@ def main():
                        "frac": achieved / HBM_PEAK_GBS,
                        "traffic": traffic,
                        "traffic_unit": "HBM bytes per fused pass (FETCH_SIZE x copy factor + WRITE_SIZE)",
-                       "kernel": pass_kernels(tuning["tiling_flags"]),
+                       "kernel": pass_kernels(args.precision),
                        "avg_launch_ms": pass_ms, "algorithmic_bytes_per_launch": bytes_per,
                        "gathered_row_bytes_per_launch": gathered,
                        "gathered_row_rate_GBs": gathered / (pass_ms * 1e-3) / 1e9,

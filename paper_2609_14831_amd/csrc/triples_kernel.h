@@ -100,17 +100,22 @@ struct TriVec {
         for (int h = 0; h < (int)sizeof(T) / 4; ++h)
             v[h] = __builtin_bit_cast(tri_u4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(voff + 16u * h), soff, 0));
     }
-    // to LDS (16-byte aligned), every element's sign flipped when sgn is set
-    __device__ __forceinline__ void store(T* p, uint32_t sgn) const {
+    // to LDS (16-byte aligned), every element's sign flipped when sgn is set;
+    // swap: a double's upper half first (see the caller)
+    __device__ __forceinline__ void store(T* p, uint32_t sgn, bool swap) const {
+        if constexpr (sizeof(T) == 4) {
+            *reinterpret_cast<tri_u4*>(p) = v[0] ^ sgn;
+        } else {
 #pragma unroll
-        for (int h = 0; h < (int)sizeof(T) / 4; ++h) {
-            tri_u4 w = v[h];
-            if constexpr (sizeof(T) == 4) w ^= sgn;
-            else {
-                w.y ^= sgn;
-                w.w ^= sgn;
+            for (int h = 0; h < 2; ++h) {
+                const tri_u4 f = v[h], g = v[1 - h];
+                tri_u4 w;
+                w.x = swap ? g.x : f.x;
+                w.y = (swap ? g.y : f.y) ^ sgn;
+                w.z = swap ? g.z : f.z;
+                w.w = (swap ? g.w : f.w) ^ sgn;
+                *reinterpret_cast<tri_u4*>(p + (swap ? 2 - 2 * h : 2 * h)) = w;
             }
-            reinterpret_cast<tri_u4*>(p)[h] = w;
         }
     }
 };
@@ -254,13 +259,17 @@ __device__ __forceinline__ void tri_tile(const TriArgs& a, T* lds, const TriTile
                 st[h][NOPS].load(rsA, va, 0);
             }
         };
+        // The two 16-byte halves of a slot's doubles in different orders in rows
+        // that share banks.  Blocks of 4 and 8 sets: 40 modes x 8 sets x 3, one
+        // step 748 -> 694 us; of 16 sets the selects cost more (2 %) than they save.
+        const bool swap = SQ < 4 && (rk & 2) != 0;
         auto store = [&]() {
 #pragma unroll
             for (int h = 0; h <= RS; ++h) {
                 if (h == RS && SQ < 4 && !sact) continue;
                 T* p = lds + ((h < RS ? h * (64 * TW) : RROWS) + lr) * STRIDE + 4 * p4;
 #pragma unroll
-                for (int c = 0; c < C; ++c) st[h][c].store(p + c * SETS, sg[h]);
+                for (int c = 0; c < C; ++c) st[h][c].store(p + c * SETS, sg[h], swap);
             }
         };
         const T* fr = lds + (w.tw * TI * 16 + is * 4 + js) * STRIDE + 4 * w.sq + bs;
