@@ -285,11 +285,29 @@ static TriShape tri_shape(const TriPlan& p, int w) {
     t.nwt = t.sq ? (p.m + 15) / 16 : (p.m + 7) / 8;
     t.nbp = 0;
     for (int v = 0; v < t.nwt; ++v) t.nbp += (t.sq ? v / t.tw : v / 2) + 1;
-    // about 512 blocks (two per CU; they start first and the quartic blocks fill
-    // in behind) or wavefronts of the one-set kernel, of at least 4 steps each
     const int steps = t.sq ? (p.ntau + 3) / 4 : (p.ntau + 15) / 16;
-    const int want = (t.sq ? 512 : 1024) / (t.nbp * t.chunks);
-    t.nstream = std::max(1, std::min(want, steps / 4));
+    if (t.sq == 0) {
+        // about 1024 wavefronts of at least 4 steps
+        t.nstream = std::max(1, std::min(1024 / t.nbp, steps / 4));
+    } else {
+        // 512 blocks are resident (two per CU).  The quadratic ones start first
+        // and the quartic ones fill in behind: half of the places for one block
+        // of sets, more with several; where quartic and quadratic blocks together
+        // can all be resident without streams much longer than a quartic
+        // block, what the quartic ones leave.  Streams of fewer than 8 steps are
+        // mostly their first loads.  A step, 5 FP64 operands, us, 512 places
+        // in every case -> this: 24 modes x 16 sets 393 -> 305, 28 x 8 404 -> 300,
+        // 32 x 8 547 -> 409, 26 x 16 473 -> 379, 36 x 3 559 -> 510, 32 x 32 1300 -> 1272;
+        // 24 x 32 519 -> 541.
+        const int q4 = (p.nt + 16 * t.tw - 1) / (16 * t.tw) * t.nwt;
+        int places = t.chunks == 1 ? 256 : t.chunks == 2 ? 320 : 512;
+        const int left = 512 - q4;
+        if (t.chunks == 1 && left > 0 && left < places) {
+            if (steps * t.nbp <= 24 * left) places = left;
+            else if (t.sq == 4) places = 512;  // a second round either way: short streams
+        }
+        t.nstream = std::max(1, std::min(places / (t.nbp * t.chunks), steps / 8));
+    }
     if (t.nstream >= 8) t.nstream &= ~7;  // whole streams per XCD
     return t;
 }
