@@ -206,7 +206,11 @@ void cut_graph_free(cut_graph_t g);
  * coefficient sets and nops operands per set, in every precision, for the
  * call kinds in `what`:
  *   CUT_RESERVE_APPLY   cut_graph_apply (partial rows of chunked or tiled
- *                       forward passes) and cut_generator_vjp;
+ *                       forward passes and of the products in triple space;
+ *                       for a graph with E_C also up to 2 GiB of partial rows
+ *                       of the outside-space action, which runs without them,
+ *                       slower, where that memory is not there) and
+ *                       cut_generator_vjp;
  *   CUT_RESERVE_FLOW    cut_flow_integrate (stage operands, RK accumulator,
  *                       generator, step counters; plus the outside-space
  *                       diagnostic buffers when the graph holds E_C);
@@ -366,7 +370,8 @@ cut_status cut_assemble(const double* X, int64_t ldx, int64_t N, int64_t S, cons
  * the RK stage combination and the state are FP64; graph passes use
  * `precision` (operands are rounded to float once per stage for the float
  * modes).  Each RK step is one stream-ordered sequence of kernels; with
- * CUT_FLOW_HIPGRAPH it is captured once as a hipGraph and replayed. */
+ * CUT_FLOW_HIPGRAPH it is captured once as a hipGraph and replayed.  The steps
+ * of a small graph are one kernel, with or without the flag. */
 #define CUT_FLOW_HIPGRAPH 1u
 #define CUT_FLOW_TIME_PASSES 2u  /* without CUT_FLOW_HIPGRAPH: bracket every graph
                                     pass and generator launch with HIP events on

@@ -315,7 +315,7 @@ static TriShape tri_shape(const TriPlan& p, int w) {
 size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops) {
     if (!g.tri.ok) return 0;
     int streams = 1;
-    for (int w : {1, 4, 8, 16}) streams = std::max(streams, tri_shape(g.tri, w).nstream);
+    for (int w : {1, 4, 8, 16, 32, 48}) streams = std::max(streams, tri_shape(g.tri, w).nstream);
     return (size_t)(4 * g.N + (int64_t)streams * g.tri.nq) * (size_t)(nops * nsets) * sizeof(double);
 }
 
