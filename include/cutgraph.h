@@ -35,7 +35,14 @@
  *    computing calls, but the work areas are shared by every call on one
  *    handle.  Calls that use a work area (chunked forward passes, generator
  *    VJP, derivatives, flows) must not overlap in time on one handle: issue
- *    them on one stream, or load the bundle once per stream.  Setup calls
+ *    them on one stream, or load the bundle once per stream.  The other calls
+ *    may overlap: outside-space actions, forward actions none of whose targets
+ *    is split, adjoint actions, generators.  Where such an action contracts
+ *    over products of strings instead of records (one coefficient set from 22
+ *    to 24 modes, more from 14 to 20, by width) it keeps partial rows in an
+ *    area of the handle whose uses are put in order on the device: on two
+ *    streams they run one after the other.  Under stream capture it runs on
+ *    the records, without them.  Setup calls
  *    (reserve, set_tiling, autotune, free) must not run concurrently with any
  *    other call on the handle.
  */
@@ -246,7 +253,9 @@ cut_status cut_graph_reserved_bytes(cut_graph_t g, int64_t* bytes);
  * records).  Pauli-boson graphs have twice as many rows as labels (real-split,
  * see cut_graph_labels).  Chunked and tiled forward passes over E_L keep
  * partial rows in the work area reserved with CUT_RESERVE_APPLY (CUT_E_INVAL
- * when it was not reserved for this shape). */
+ * when it was not reserved for this shape), whether they then run over the
+ * records or as products in triple space.  Outside-space actions and forward
+ * actions that keep none run over the records where nothing was reserved. */
 cut_status cut_graph_apply(cut_graph_t g, int32_t which, int32_t precision, int64_t nsets,
                            int64_t nops, const void* eta, int64_t lde, const void* x,
                            int64_t ldx, double* y, int64_t ldy, uint32_t flags, void* stream);
@@ -277,7 +286,9 @@ cut_status cut_graph_apply_adjoint(cut_graph_t g, int32_t which, int32_t precisi
  * area, so no cut_graph_reserve is needed and nothing is allocated.  Every
  * call on one GPU shares that array (it keeps the last call's partial rows;
  * each call writes every row it reads first), so calls that overlap in time on
- * one GPU race: issue them on one stream.  Errors: as cut_graph_apply, plus
+ * one GPU race: issue them on one stream.  Calls whose passes over the records
+ * keep no partial rows (outside-space actions among them) run over the records
+ * without the array.  Errors: as cut_graph_apply, plus
  * CUT_E_INVAL when the shape and tiling need more than 64 MiB of partial rows
  * (fewer columns per call, longer chunks or CUT_TILE_NO_CHUNKS fit). */
 cut_status cut_graph_apply_noalloc(cut_graph_t g, int32_t which, int32_t precision, int64_t nsets,

@@ -113,7 +113,7 @@ using namespace cut;
 namespace cut {
 
 // Validates the arguments of a forward action and returns its pass arguments;
-// *part_bytes receives the partial-row bytes its forward pass needs (0: none).
+// *part_bytes receives the partial-row bytes its passes over the records need (0: none).
 PassArgs apply_args(Graph& g, int32_t which, int32_t precision, int64_t nsets, int64_t nops, const void* eta,
                     int64_t lde, const void* x, int64_t ldx, double* y, int64_t ldy, uint32_t flags,
                     size_t* part_bytes) {
@@ -139,8 +139,7 @@ PassArgs apply_args(Graph& g, int32_t which, int32_t precision, int64_t nsets, i
     p.ldy = ldy;
     p.accumulate = (flags & CUT_ACCUMULATE) ? 1 : 0;
     p.scale = 1.0;
-    *part_bytes = which == CUT_GRAPH_FLOW ? forward_partial_bytes(g, p.nsets, p.nops, precision) : 0;
-    p.part_bytes = *part_bytes;
+    *part_bytes = which == CUT_GRAPH_FLOW ? record_partial_bytes(g, p.nsets, p.nops, precision) : 0;
     return p;
 }
 
@@ -154,10 +153,26 @@ extern "C" cut_status cut_graph_apply(cut_graph_t h, int32_t which, int32_t prec
     size_t pb = 0;
     PassArgs p = apply_args(g, which, precision, nsets, nops, eta, lde, x, ldx, y, ldy, flags, &pb);
     DeviceGuard dg(g.device);
-    double* part = nullptr;
-    if (which == CUT_GRAPH_FLOW) part = forward_part(g, p.nsets, p.nops, precision, "cut_graph_apply (partial rows)", &p.part_bytes);
-    if (which == CUT_GRAPH_OUTSIDE && outside_usable(g, p)) launch_outside(g, p, (hipStream_t)stream);
-    else launch_forward(g, EPI_Y, p, part, (hipStream_t)stream);
+    hipStream_t s = (hipStream_t)stream;
+    if (pb > 0) {
+        double* part = forward_part(g, p.nsets, p.nops, precision, "cut_graph_apply (partial rows)", &p.part_bytes);
+        launch_forward(g, EPI_Y, p, part, s);
+    } else {
+        // no work area of its own: the products take the shared rows, else the records
+        const bool outside = which == CUT_GRAPH_OUTSIDE && outside_usable(g, p);
+        size_t least = outside ? outside_least(g, nsets) : 0;
+        if (which == CUT_GRAPH_FLOW) {
+            least = p.part_bytes = forward_partial_bytes(g, p.nsets, p.nops, precision);
+            if (!triples_usable(g, p)) least = p.part_bytes = 0;
+        }
+        if (least == 0) {
+            launch_forward(g, EPI_Y, p, nullptr, s);
+        } else {
+            SharedUse use(g.rows, least, s);
+            if (outside && use.rows()) launch_outside(g, p, use.rows(), use.bytes(), s);
+            else launch_forward(g, EPI_Y, p, use.rows(), s);
+        }
+    }
     HIP_CHECK(hipGetLastError());
     ABI_END
 }

@@ -139,6 +139,7 @@ Graph::~Graph() {
     ws_small.release();
     ws_part.release();
     ws_deriv.release();
+    rows.release();
     (void)hipSetDevice(cur);
 }
 

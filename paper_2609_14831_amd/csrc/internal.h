@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -284,6 +285,35 @@ struct Workspace {
     void release();
 };
 
+// Partial rows of the calls that may overlap on one handle (the header's
+// concurrency rule: actions whose passes over the records keep none).  Uses are
+// put in order: each waits on the device for the one before it, whatever its
+// stream or thread.
+struct SharedRows {
+    Workspace ws;
+    hipEvent_t done = nullptr;  // end of the last use (made with the first reservation)
+    std::mutex mu;              // held while a use is enqueued
+    void reserve(size_t n);     // as Workspace::reserve
+    void release();
+};
+
+// One use of the shared rows by work on `s`: rows() is null where they do not
+// hold `least` bytes and under stream capture (the replays of a graph could not
+// be put in order with other uses).
+class SharedUse {
+  public:
+    SharedUse(SharedRows& r, size_t least, hipStream_t s);
+    ~SharedUse();  // ends the use, after its last launch
+    double* rows() const { return part; }
+    size_t bytes() const { return part ? r.ws.bytes : 0; }
+
+  private:
+    SharedRows& r;
+    std::unique_lock<std::mutex> lock;
+    hipStream_t s;
+    double* part = nullptr;
+};
+
 struct StepGraphCache;
 
 struct Graph {
@@ -336,6 +366,7 @@ struct Graph {
     Workspace ws_small;              // scratch of single generator-VJP calls
     Workspace ws_part;               // tile partial slots of single forward passes
     Workspace ws_deriv;              // generator, tangent and float shadows of derivative calls
+    SharedRows rows;                 // outside-space actions; forward actions without partial rows over the records
     // shapes reserved so far: (nsets, nops, ckpt_every, CUT_RESERVE_* flags)
     std::vector<std::vector<int64_t>> reserved;
     StepGraphCache* graphs = nullptr;
@@ -437,11 +468,13 @@ double* forward_part(Graph& g, int32_t nsets, int32_t nops, int32_t precision, c
 void build_triples(Graph& g, const HostGraph& hg);
 size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops);
 bool triples_usable(const Graph& g, const PassArgs& a);
-// the same for the outside-space action (partial rows in g.ws_part)
+// the same for the outside-space action: `bytes` of partial rows at `part`, at
+// least outside_least() of them (more: more operands at a time)
 void build_outside(Graph& g, const HostGraph& hg);
 size_t outside_partial_bytes(const Graph& g, int64_t nsets, int64_t nops);
+size_t outside_least(const Graph& g, int64_t nsets);
 bool outside_usable(const Graph& g, const PassArgs& a);
-void launch_outside(const Graph& g, const PassArgs& a, hipStream_t s);
+void launch_outside(const Graph& g, const PassArgs& a, double* part, size_t bytes, hipStream_t s);
 // the two transposed actions of E_L (a: the pass over the reverse orientation),
 // as brackets where triples_usable, with `part` as the forward pass has it
 void launch_adjoint_x(const Graph& g, const PassArgs& a, double* part, hipStream_t s);

@@ -44,16 +44,16 @@ extern "C" cut_status cut_graph_apply_noalloc(cut_graph_t h, int32_t which, int3
     Graph& g = checked(h);
     size_t pb = 0;
     PassArgs p = apply_args(g, which, precision, nsets, nops, eta, lde, x, ldx, y, ldy, flags, &pb);
-    // the route over the records is taken where only its partial rows fit
-    if (pb > 0) pb = record_partial_bytes(g, p.nsets, p.nops, precision);
-    p.part_bytes = kScratchBytes;
+    // only calls whose passes over the records keep partial rows use the scratch:
+    // the others may overlap
+    p.part_bytes = pb ? kScratchBytes : 0;
     if (pb > kScratchBytes)
         CUT_FAIL(CUT_E_INVAL,
                  "cut_graph_apply_noalloc: this shape and tiling need %zu bytes of partial rows, the fixed "
                  "scratch holds %zu (fewer columns, longer chunks or CUT_TILE_NO_CHUNKS)",
                  pb, kScratchBytes);
     DeviceGuard dg(g.device);
-    double* part = which == CUT_GRAPH_FLOW && (pb || g.tri.ok) ? scratch_on(g.device) : nullptr;
+    double* part = pb ? scratch_on(g.device) : nullptr;
     launch_forward(g, EPI_Y, p, part, (hipStream_t)stream);
     HIP_CHECK(hipGetLastError());
     ABI_END

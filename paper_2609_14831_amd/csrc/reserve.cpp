@@ -8,10 +8,12 @@
 namespace cut {
 
 void reserve_shape(Graph& g, int64_t nsets, int64_t nops, int64_t ckpt_every, uint32_t what) {
-    size_t part = 0, small = 0, deriv = 0, ws = 0;
+    size_t part = 0, rows = 0, small = 0, deriv = 0, ws = 0;
     for (int prec = CUT_F64; prec <= CUT_F32; ++prec) {
-        if (what & (CUT_RESERVE_APPLY | CUT_RESERVE_DERIV))
-            part = std::max(part, forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec));
+        const size_t fwd = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec);
+        const bool area = record_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec) > 0;
+        if ((what & CUT_RESERVE_DERIV) || ((what & CUT_RESERVE_APPLY) && area)) part = std::max(part, fwd);
+        if ((what & CUT_RESERVE_APPLY) && !area) rows = std::max(rows, fwd);
         if (what & CUT_RESERVE_DERIV)
             deriv = std::max({deriv, jvp_ws_bytes(g, nsets, nops, prec), vjp_ws_bytes(g, nsets, nops, prec)});
         if (what & CUT_RESERVE_FLOW)
@@ -21,19 +23,45 @@ void reserve_shape(Graph& g, int64_t nsets, int64_t nops, int64_t ckpt_every, ui
     if ((what & CUT_RESERVE_ADJOINT) && ckpt_every > 0)
         ws = std::max(ws, flow_ws_bytes(g, nsets, nops, CUT_F64, flow_adjoint_extra(g, nsets, nops, ckpt_every)));
     if (what & CUT_RESERVE_APPLY) {
-        // the outside-space products' partial rows, if the memory is there: its
-        // action runs on the records without them
-        const size_t out = std::max(part, outside_partial_bytes(g, nsets, nops));
+        // the shared rows, if the memory is there: their actions run on the
+        // records without them
         try {
-            g.ws_part.reserve(out);
+            g.rows.reserve(std::max(rows, outside_partial_bytes(g, nsets, nops)));
         } catch (const Fail&) {
-            if (out == part) throw;
         }
     }
     g.ws_part.reserve(part);
     g.ws_small.reserve(small);
     g.ws_deriv.reserve(deriv);
     g.ws.reserve(ws);
+}
+
+void SharedRows::reserve(size_t n) {
+    std::lock_guard<std::mutex> lock(mu);
+    if (n > 0 && !done) HIP_CHECK(hipEventCreateWithFlags(&done, hipEventDisableTiming));
+    ws.reserve(n);
+}
+
+SharedUse::SharedUse(SharedRows& r_, size_t least, hipStream_t s_) : r(r_), lock(r_.mu), s(s_) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (r.ws.bytes < least || !r.ws.ptr) return;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();  // the null stream while another stream is captured
+        return;
+    }
+    if (st != hipStreamCaptureStatusNone) return;
+    HIP_CHECK(hipStreamWaitEvent(s, r.done, 0));
+    part = (double*)r.ws.ptr;
+}
+
+SharedUse::~SharedUse() {
+    if (part) (void)hipEventRecord(r.done, s);
+}
+
+void SharedRows::release() {
+    ws.release();
+    if (done) (void)hipEventDestroy(done);
+    done = nullptr;
 }
 
 void rereserve(Graph& g) {
@@ -63,6 +91,6 @@ extern "C" cut_status cut_graph_reserved_bytes(cut_graph_t h, int64_t* bytes) {
     ABI_BEGIN
     Graph& g = checked(h);
     if (!bytes) CUT_FAIL(CUT_E_INVAL, "cut_graph_reserved_bytes: null output");
-    *bytes = (int64_t)(g.ws.bytes + g.ws_small.bytes + g.ws_part.bytes + g.ws_deriv.bytes);
+    *bytes = (int64_t)(g.ws.bytes + g.ws_small.bytes + g.ws_part.bytes + g.ws_deriv.bytes + g.rows.ws.bytes);
     ABI_END
 }

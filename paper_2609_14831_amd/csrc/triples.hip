@@ -570,12 +570,12 @@ void build_outside(Graph& g, const HostGraph& hg) {
 
 // Partial rows of the outside-space products: 4 per target, for as many operands at a
 // time as fit 2 GiB (0: not even one does).
-static size_t outside_one(const Graph& g, int64_t nsets) { return (size_t)(4 * g.n_out * nsets) * sizeof(double); }
+size_t outside_least(const Graph& g, int64_t nsets) { return (size_t)(4 * g.n_out * nsets) * sizeof(double); }
 
 size_t outside_partial_bytes(const Graph& g, int64_t nsets, int64_t nops) {
     constexpr size_t kCap = (size_t)2 << 30;
     if (!g.tri.out_ok) return 0;
-    const size_t one = outside_one(g, nsets);
+    const size_t one = outside_least(g, nsets);
     return one > kCap ? 0 : one * std::min<size_t>((size_t)nops, kCap / one);
 }
 
@@ -588,18 +588,18 @@ size_t outside_partial_bytes(const Graph& g, int64_t nsets, int64_t nops) {
 //   below it        20 x 1 x 3 FP64 0.89 of its speed, 18 x 8 x 3 float 0.85, 16 x 8 x 3 FP64 0.76
 bool outside_usable(const Graph& g, const PassArgs& a) {
     const int least = a.nsets == 1 ? 22 : a.precision == CUT_F64 && a.nsets > 4 ? 18 : 20;
-    if (!g.tri.out_ok || g.tri.m < least || a.precision == CUT_F32 || g.ws_part.bytes < outside_one(g, a.nsets)) return false;
+    if (!g.tri.out_ok || g.tri.m < least || a.precision == CUT_F32) return false;
     const int64_t esz = a.precision == CUT_F64 ? 8 : 4;
     return g.N * std::max(a.lda, a.ldb) * esz < (int64_t)0x7FFFFFFF;
 }
 
-void launch_outside(const Graph& g, const PassArgs& a, hipStream_t s) {
+void launch_outside(const Graph& g, const PassArgs& a, double* part, size_t bytes, hipStream_t s) {
     const TriPlan& p = g.tri;
     const bool f32 = a.precision != CUT_F64;
     const int64_t esz = f32 ? 4 : 8;
     const int sq = a.nsets <= 4 ? 1 : a.nsets <= 8 ? 2 : 4, w = sq == 4 ? 0 : sq == 2 ? 1 : 2;
     const int chunks = (a.nsets + 4 * sq - 1) / (4 * sq), ntask = p.task0[w + 1] - p.task0[w];
-    const int fit = (int)std::min<size_t>((size_t)a.nops, g.ws_part.bytes / outside_one(g, a.nsets));
+    const int fit = (int)std::min<size_t>((size_t)a.nops, bytes / outside_least(g, a.nsets));
     const int most = f32 ? tri_ops<float>() : tri_ops<double>();
     const int64_t bytesA = ((g.N - 1) * a.lda + a.nsets) * esz;
     const int64_t bytesB = ((g.N - 1) * a.ldb + (int64_t)a.nops * a.nsets) * esz;
@@ -630,14 +630,14 @@ void launch_outside(const Graph& g, const PassArgs& a, hipStream_t s) {
             const int64_t bo = (int64_t)(o + q) * a.nsets * esz;
             t.B = (const char*)a.B + bo;
             t.bytesB = (uint32_t)(bytesB - bo);
-            t.p4 = (double*)g.ws_part.ptr + (int64_t)q * a.nsets;
+            t.p4 = part + (int64_t)q * a.nsets;
             const dim3 grid((unsigned)((int64_t)ntask * chunks));
             if (f32) launch_outside_t<float>(t, k, sq, grid, s);
             else launch_outside_t<double>(t, k, sq, grid, s);
             q += k;
         }
         TriCombineArgs c{};
-        c.p4 = (const double*)g.ws_part.ptr;
+        c.p4 = part;
         c.nops = nops;
         c.nsets = a.nsets;
         c.w = a.nsets;

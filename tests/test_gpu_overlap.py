@@ -1,0 +1,44 @@
+"""Actions that may overlap on one handle: outside-space actions, and forward
+actions whose passes over the records keep no partial rows, on two streams of
+one handle at once.  Each result is bitwise that of the same call alone."""
+import numpy as np
+import pytest
+
+import gpu_util as U
+import workloads
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def L():
+    from paper_2609_14831_amd import _lib
+    return _lib
+
+
+@pytest.mark.parametrize("which,m,nsets,nops", [("outside", 20, 8, 3), ("flow", 14, 48, 2)])
+def test_two_streams_of_one_handle(L, which, m, nsets, nops):
+    g = U.outside_graph(L, m) if which == "outside" else U.graph(L, "majorana", m)
+    w = L.CUT_GRAPH_OUTSIDE if which == "outside" else L.CUT_GRAPH_FLOW
+    info = L.cut_graph_info(g)
+    n, rows = info["n_ops"], info["n_out_ops"] if which == "outside" else info["n_ops"]
+    t = lambda shape, seed: torch.tensor(workloads.random_dense(shape, seed=seed), device=DEV)
+    ops = [(t((n, nsets), 3 * k), t((n, nsets * nops), 3 * k + 1)) for k in range(2)]
+    ys = [torch.zeros((rows, nsets * nops), dtype=torch.float64, device=DEV) for _ in range(2)]
+    alone = []
+    for (eta, x), y in zip(ops, ys):
+        L.cut_graph_apply(g, w, L.CUT_F64, nsets, nops, eta, x, y)
+        torch.cuda.synchronize()
+        alone.append(y.cpu().numpy().copy())
+        y.fill_(float("nan"))
+    assert np.isfinite(alone[0]).all() and not np.array_equal(alone[0], alone[1])
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for rep in range(20):
+        for k in ((0, 1), (1, 0))[rep % 2]:
+            L.cut_graph_apply(g, w, L.CUT_F64, nsets, nops, *ops[k], ys[k], stream=streams[k].cuda_stream)
+    torch.cuda.synchronize()
+    for k in range(2):
+        np.testing.assert_array_equal(ys[k].cpu().numpy(), alone[k])

@@ -1,0 +1,85 @@
+"""Host side of the computing calls without a GPU (tests/fake_hip.cpp): which
+kernels a call launches, in which order its streams are put, and what it
+allocates."""
+import pytest
+
+import host_runtime as H
+
+
+def _ordered(lines, streams, kernel):
+    """Every use: a wait for the event that the use before it recorded after its last launch."""
+    ev = {l.split()[2] for l in lines if l.split()[0] in ("wait", "record")}
+    assert len(ev) == 1, lines
+    want = []
+    for s in streams:
+        want += [("wait", s), ("kernel", s, kernel), ("kernel", s, "k_tri_combine"), ("record", s)]
+    got = []
+    for l in lines:
+        w = l.split(" ", 3)
+        got.append((w[0], w[1]) if w[0] != "kernel" else (w[0], w[1], w[3].split("<")[0]))
+    assert got == want, lines
+
+
+def test_outside_actions_on_two_streams_are_put_in_order():
+    lines = H.run("""
+g = graph(18, L.CUT_BUILD_OUTSIDE)
+L.cut_graph_reserve(g, 8, 3, 0, L.CUT_RESERVE_APPLY)
+log()
+for s in (0x11, 0x22, 0x11):
+    L.cut_graph_apply(g, 2, L.CUT_F64, 8, 3, Buf(8), Buf(24), Buf(24), stream=s)
+out(log())
+""")
+    _ordered(lines, ["11", "22", "11"], "k_outside")
+
+
+@pytest.mark.parametrize("tiling,m,nsets", [(0, 14, 33), (4, 24, 8)])   # no target split; CUT_TILE_NO_CHUNKS
+def test_actions_without_partial_rows_on_two_streams_are_put_in_order(tiling, m, nsets):
+    lines = H.run(f"""
+g = graph({m})
+L.cut_graph_set_tiling(g, 1 << 20, 512, {tiling})
+L.cut_graph_reserve(g, {nsets}, 1, 0, L.CUT_RESERVE_APPLY)
+log()
+for s in (0x11, 0x22):
+    L.cut_graph_apply(g, 0, L.CUT_F64, {nsets}, 1, Buf({nsets}), Buf({nsets}), Buf({nsets}), stream=s)
+out(log())
+""")
+    _ordered(lines, ["11", "22"], "k_triples")
+
+
+def test_area_of_overlapping_actions_is_not_the_chunked_passes_own():
+    """An outside-space action may run beside a chunked pass: they share no partial rows."""
+    out = H.run("""
+g = graph(18, L.CUT_BUILD_OUTSIDE)
+log()
+L.cut_graph_reserve(g, 8, 3, 0, L.CUT_RESERVE_APPLY)
+got = [int(l.split()[1]) for l in log() if l.startswith("malloc")]
+out([got, L.cut_graph_reserved_bytes(g)])
+""")
+    sizes, total = out
+    assert 4 * 18564 * 24 * 8 in sizes and len(sizes) == 3 and sum(sizes) == total
+
+
+def test_captured_actions_without_partial_rows_run_on_the_records():
+    out = H.run("""
+g = graph(18, L.CUT_BUILD_OUTSIDE)
+h = graph(14)
+L.cut_graph_reserve(g, 8, 3, 0, L.CUT_RESERVE_APPLY)
+L.cut_graph_reserve(h, 33, 1, 0, L.CUT_RESERVE_APPLY)
+fake.fake_capturing(0x11, 1)
+log()
+L.cut_graph_apply(g, 2, L.CUT_F64, 8, 3, Buf(8), Buf(24), Buf(24), stream=0x11)
+L.cut_graph_apply(h, 0, L.CUT_F64, 33, 1, Buf(33), Buf(33), Buf(33), stream=0x11)
+out(log())
+""")
+    assert [l.split(" ", 3)[3].split("<")[0] for l in out] == ["k_pass", "k_pass"], out
+
+
+@pytest.mark.parametrize("which,m,nsets", [(0, 14, 33), (2, 18, 8)])
+def test_noalloc_leaves_the_scratch_alone_where_the_records_need_none(which, m, nsets):
+    out = H.run(f"""
+g = graph({m}, {"L.CUT_BUILD_OUTSIDE" if which else 0})
+log()
+L.cut_graph_apply_noalloc(g, {which}, L.CUT_F64, {nsets}, 1, Buf({nsets}), Buf({nsets}), Buf({nsets}), stream=0x11)
+out(log())
+""")
+    assert [l.split(" ", 3)[3].split("<")[0] for l in out] == ["k_pass"], out
