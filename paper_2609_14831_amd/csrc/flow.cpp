@@ -220,6 +220,7 @@ struct StepPlan {
     // narrowest lane group: that of the layout of all the sets, so that a
     // compacted phase sums every term in the same order (bitwise the same flow)
     int32_t gfloor = 1;
+    int64_t ldfull = 0;  // row length of that layout
 };
 
 // HIP events bracketing launches (kind 0 = graph pass, 1 = generator)
@@ -296,6 +297,7 @@ static void enqueue_step(const StepPlan& P, hipStream_t s, PassTimer* tm = nullp
         p.gmax = 64 >> g.bchunk;  // the tiling's B-chunk
         p.narrow = P.narrow;
         p.gfloor = P.gfloor;
+        p.ldfull = P.ldfull;
         p.part_bytes = P.fb.part_bytes;
         if (tm) tm->mark(0, s);
         const size_t nr = std::max<size_t>(1, P.ranges.size());
@@ -456,6 +458,7 @@ extern "C" cut_status cut_flow_integrate(cut_graph_t h, const cut_flow_params* p
         };
         // lane groups of a launch over w sets of the full layout span
         // max(w, min(8, nsets)) sets rounded up to a power of two
+        P.ldfull = cols;
         while (P.gfloor < std::min<int64_t>(8, nsets)) P.gfloor <<= 1;
         enter(0);
         launch_prep_state(P.z, g.N, (int32_t)nops, P.nsets, fb.xsh[0], f32, fb.hst, stream);

@@ -419,6 +419,9 @@ struct PassArgs {
     // lane groups of the segment kernel span at least this many sets (a
     // compacted flow keeps the widths, hence the sums, of its full layout)
     int32_t gfloor = 1;
+    // row length of that full layout (0: this one): its size decides whether a
+    // flow's passes run in triple space, so a compacted phase takes their route
+    int64_t ldfull = 0;
     size_t part_bytes = 0;          // partial-row bytes the caller provides to launch_forward
     int32_t precision;              // cut_precision
     const int32_t* nsteps;          // device [nsets] or null (all active)

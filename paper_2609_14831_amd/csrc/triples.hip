@@ -343,7 +343,7 @@ bool triples_usable(const Graph& g, const PassArgs& a) {
     const int w = tri_width(a);
     const int least = w > 32 ? kTriMinModes : f64 && w > 16 ? 20 : w == 1 || w > (f64 ? 4 : 16) ? 24 : 26;
     if (g.tri.m < least) return false;
-    if (g.N * std::max(a.lda, a.ldb) * (f64 ? 8 : 4) >= (int64_t)0x7FFFFFFF) return false;
+    if (g.N * std::max({a.lda, a.ldb, a.ldfull}) * (f64 ? 8 : 4) >= (int64_t)0x7FFFFFFF) return false;
     return a.part_bytes >= triples_partial_bytes(g, a.nsets, a.nops);
 }
 

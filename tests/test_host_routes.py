@@ -83,3 +83,28 @@ L.cut_graph_apply_noalloc(g, {which}, L.CUT_F64, {nsets}, 1, Buf({nsets}), Buf({
 out(log())
 """)
     assert [l.split(" ", 3)[3].split("<")[0] for l in out] == ["k_pass"], out
+
+
+def _flow_passes(m, nsets, nops, steps, prec, tiling=None):
+    """The kernels over E_L (segment, chunk and triple-space passes) of a flow, in order."""
+    lines = H.run(f"""
+g = graph({m})
+{"L.cut_graph_set_tiling(g, *" + repr(tiling) + ")" if tiling else ""}
+L.cut_graph_reserve(g, {nsets}, {nops}, 0, L.CUT_RESERVE_FLOW)
+log()
+p = L.flow_params(L.CUT_GEN_G2, L.CUT_{prec}, 1e-3, flags=0, nonfinite=Buf(1))
+steps = {steps}
+L.cut_flow_integrate(g, p, {nsets}, {nops}, steps, Buf(1), stream=0x11, reserve=False)
+out([k for k, _ in kernels(log())])
+""")
+    return [k for k in lines if k in ("k_pass", "k_triples", "k_triples1", "k_tile", "k_tile64", "k_qblock")]
+
+
+def test_compacted_phases_take_the_route_of_the_full_layout():
+    """24,800 FP64 columns are past the 2 GiB that 32-bit offsets reach: every pass runs on the
+    records, also when the last 12 of the 3,100 sets are repacked into a layout of 16."""
+    ks = _flow_passes(24, 3100, 8, "[3] * 12 + [1] * 3088", "F64")
+    assert ks and set(ks) == {"k_pass"}, sorted(set(ks))
+    # a layout within that reach, with as many sets left at the end: every pass in triple space
+    ks = _flow_passes(24, 300, 8, "[3] * 12 + [1] * 288", "F64")
+    assert ks and set(ks) == {"k_triples"}, sorted(set(ks))
