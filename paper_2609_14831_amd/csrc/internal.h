@@ -483,6 +483,9 @@ void launch_outside(const Graph& g, const PassArgs& a, double* part, size_t byte
 void launch_adjoint_x(const Graph& g, const PassArgs& a, double* part, hipStream_t s);
 void launch_adjoint_eta(const Graph& g, const PassArgs& a, double* part, hipStream_t s);
 void launch_triples(const Graph& g, int epi, const PassArgs& a, int nred, double sign, double* part, hipStream_t s);
+// a full-width forward pass in pieces whose partial rows fit `bytes`, each result
+// bitwise that of the one launch
+void launch_triples_in(const Graph& g, const PassArgs& a, double* part, size_t bytes, hipStream_t s);
 // whole flow of a small graph in one launch: whether it applies, and steps
 // [t0, t1) of every set s below nsteps[s] (device), with the checkpoints of
 // those steps

@@ -44,17 +44,22 @@ extern "C" cut_status cut_graph_apply_noalloc(cut_graph_t h, int32_t which, int3
     Graph& g = checked(h);
     size_t pb = 0;
     PassArgs p = apply_args(g, which, precision, nsets, nops, eta, lde, x, ldx, y, ldy, flags, &pb);
-    // only calls whose passes over the records keep partial rows use the scratch:
-    // the others may overlap
-    p.part_bytes = pb ? kScratchBytes : 0;
     if (pb > kScratchBytes)
         CUT_FAIL(CUT_E_INVAL,
                  "cut_graph_apply_noalloc: this shape and tiling need %zu bytes of partial rows, the fixed "
                  "scratch holds %zu (fewer columns, longer chunks or CUT_TILE_NO_CHUNKS)",
                  pb, kScratchBytes);
     DeviceGuard dg(g.device);
+    // only calls whose passes over the records keep partial rows use the scratch:
+    // the others may overlap
     double* part = pb ? scratch_on(g.device) : nullptr;
-    launch_forward(g, EPI_Y, p, part, (hipStream_t)stream);
+    p.part_bytes = pb ? forward_partial_bytes(g, p.nsets, p.nops, precision) : 0;
+    if (part && triples_usable(g, p)) {
+        launch_triples_in(g, p, part, kScratchBytes, (hipStream_t)stream);
+    } else {
+        p.part_bytes = 0;
+        launch_forward(g, EPI_Y, p, part, (hipStream_t)stream);
+    }
     HIP_CHECK(hipGetLastError());
     ABI_END
 }

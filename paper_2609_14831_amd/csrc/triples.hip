@@ -312,11 +312,15 @@ static TriShape tri_shape(const TriPlan& p, int w) {
     return t;
 }
 
-size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops) {
-    if (!g.tri.ok) return 0;
+// partial rows of one column, for the most streams of any width
+static size_t tri_column_bytes(const Graph& g) {
     int streams = 1;
     for (int w : {1, 4, 8, 16, 32, 48}) streams = std::max(streams, tri_shape(g.tri, w).nstream);
-    return (size_t)(4 * g.N + (int64_t)streams * g.tri.nq) * (size_t)(nops * nsets) * sizeof(double);
+    return (size_t)(4 * g.N + (int64_t)streams * g.tri.nq) * sizeof(double);
+}
+
+size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops) {
+    return g.tri.ok ? tri_column_bytes(g) * (size_t)(nops * nsets) : 0;
 }
 
 // Sets that decide a launch's shape: as wide as the segment kernel's lane
@@ -448,6 +452,28 @@ void launch_triples(const Graph& g, int epi, const PassArgs& a, int nred, double
     const unsigned nb = nb2 + (unsigned)(((g.N - p.nq) * cw + 255) / 256);
     if (epi == EPI_Y) hipLaunchKernelGGL((k_tri_combine<EPI_Y>), dim3(nb), dim3(256), 0, s, c, nb2);
     else hipLaunchKernelGGL((k_tri_combine<EPI_RK>), dim3(nb), dim3(256), 0, s, c, nb2);
+}
+
+void launch_triples_in(const Graph& g, const PassArgs& a, double* part, size_t bytes, hipStream_t s) {
+    // whole operands while their columns fit, else ranges of the sets of one;
+    // every piece has the shape of the whole launch (its width), so each sum is
+    // bitwise the whole launch's
+    const int64_t fit = (int64_t)(bytes / tri_column_bytes(g)), esz = a.precision == CUT_F64 ? 8 : 4;
+    if (fit < 1) CUT_FAIL(CUT_E_INVAL, "partial rows of one column need %zu bytes, there are %zu", tri_column_bytes(g), bytes);
+    int64_t ops = std::max<int64_t>(1, std::min<int64_t>(a.nops, fit / a.nsets)), sets = std::min<int64_t>(a.nsets, fit);
+    if (sets < a.nsets && sets > 16) sets &= ~15;  // whole blocks of sets
+    for (int64_t o = 0; o < a.nops; o += ops)
+        for (int64_t s0 = 0; s0 < a.nsets; s0 += sets) {
+            const int64_t b = o * a.nsets + s0;
+            PassArgs q = a;
+            q.gfloor = tri_width(a);
+            q.nops = (int32_t)std::min<int64_t>(ops, a.nops - o);
+            q.nsets = (int32_t)std::min<int64_t>(sets, a.nsets - s0);
+            q.A = (const char*)a.A + s0 * esz;
+            q.B = (const char*)a.B + b * esz;
+            q.y = (double*)a.y + b;
+            launch_triples(g, EPI_Y, q, 1, 1.0, part, s);
+        }
 }
 
 void launch_adjoint_x(const Graph& g, const PassArgs& a, double* part, hipStream_t s) {

@@ -108,3 +108,18 @@ def test_compacted_phases_take_the_route_of_the_full_layout():
     # a layout within that reach, with as many sets left at the end: every pass in triple space
     ks = _flow_passes(24, 300, 8, "[3] * 12 + [1] * 288", "F64")
     assert ks and set(ks) == {"k_triples"}, sorted(set(ks))
+
+
+@pytest.mark.parametrize("m,nsets,nops,launches", [(24, 8, 3, 1), (24, 64, 8, 4), (24, 200, 2, 2 * 2)])
+def test_noalloc_takes_the_route_of_apply(m, nsets, nops, launches):
+    """Past the scratch's 64 MiB (about 160 columns of 24 modes) the products run in pieces."""
+    a, b = H.run(f"""
+g = graph({m})
+args = (g, 0, L.CUT_F64, {nsets}, {nops}, Buf({nsets}), Buf({nsets * nops}), Buf({nsets * nops}))
+L.cut_graph_apply(*args, stream=0x11)
+a = [k for k, _ in kernels(log())]
+L.cut_graph_apply_noalloc(*args, stream=0x11)
+out([a, [k for k, _ in kernels(log())]])
+""")
+    assert set(a) == set(b) == {"k_triples", "k_tri_combine"}
+    assert b.count("k_triples") == launches
