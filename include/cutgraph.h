@@ -216,8 +216,8 @@ void cut_graph_free(cut_graph_t g);
  *                       forward passes and of the products in triple space;
  *                       for a graph with E_C also up to 2 GiB of partial rows
  *                       of the outside-space action, which runs without them,
- *                       slower, where that memory is not there) and
- *                       cut_generator_vjp;
+ *                       slower, where twice that memory is not free when the
+ *                       shape is first reserved) and cut_generator_vjp;
  *   CUT_RESERVE_FLOW    cut_flow_integrate (stage operands, RK accumulator,
  *                       generator, step counters; plus the outside-space
  *                       diagnostic buffers when the graph holds E_C);

@@ -84,36 +84,6 @@ void DevCSR::release() {
     nseg = nrec = ntasks = per_xcd = 0;
 }
 
-void* Workspace::need(size_t n, const char* what) const {
-    if (n <= bytes) return ptr;
-    CUT_FAIL(CUT_E_INVAL,
-             "%s needs a work area of %zu bytes, %zu are reserved: call cut_graph_reserve with this shape "
-             "(and again after a tiling change that adds partial rows)",
-             what, n, bytes);
-}
-
-void Workspace::reserve(size_t n) {
-    if (n <= bytes) return;
-    if (ptr) {
-        HIP_CHECK(hipDeviceSynchronize());
-        (void)hipFree(ptr);
-        ptr = nullptr;
-        bytes = 0;
-    }
-    hipError_t e = hipMalloc(&ptr, n);
-    if (e != hipSuccess) {
-        ptr = nullptr;
-        CUT_FAIL(CUT_E_NOMEM, "work area hipMalloc(%zu): %s", n, hipGetErrorString(e));
-    }
-    bytes = n;
-}
-
-void Workspace::release() {
-    if (ptr) (void)hipFree(ptr);
-    ptr = nullptr;
-    bytes = 0;
-}
-
 void release_step_graphs(Graph& g);
 
 Graph::~Graph() {

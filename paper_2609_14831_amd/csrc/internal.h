@@ -282,6 +282,9 @@ struct Workspace {
     size_t bytes = 0;
     void* need(size_t n, const char* what) const;
     void reserve(size_t n);     // grows: synchronises the device, frees, allocates
+    // grows if the memory is there and as much again stays free; keeps what it
+    // holds otherwise
+    void reserve_optional(size_t n);
     void release();
 };
 
@@ -293,7 +296,7 @@ struct SharedRows {
     Workspace ws;
     hipEvent_t done = nullptr;  // end of the last use (made with the first reservation)
     std::mutex mu;              // held while a use is enqueued
-    void reserve(size_t n);     // as Workspace::reserve
+    void reserve_optional(size_t n);  // as Workspace::reserve_optional
     void release();
 };
 
@@ -386,7 +389,8 @@ size_t flow_outside_extra(const Graph& g, int64_t nsets, int64_t nops);
 size_t flow_adjoint_extra(const Graph& g, int64_t nsets, int64_t nops, int64_t ckpt_every);
 size_t jvp_ws_bytes(const Graph& g, int64_t nsets, int64_t nops, int prec);
 size_t vjp_ws_bytes(const Graph& g, int64_t nsets, int64_t nops, int prec);
-void reserve_shape(Graph& g, int64_t nsets, int64_t nops, int64_t ckpt_every, uint32_t what);
+// `extra`: also the areas that calls run without, slower, where memory is short
+void reserve_shape(Graph& g, int64_t nsets, int64_t nops, int64_t ckpt_every, uint32_t what, bool extra);
 void rereserve(Graph& g);
 
 // tiling plan (host) -> device task list

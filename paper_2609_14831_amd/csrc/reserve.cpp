@@ -7,7 +7,58 @@
 
 namespace cut {
 
-void reserve_shape(Graph& g, int64_t nsets, int64_t nops, int64_t ckpt_every, uint32_t what) {
+void* Workspace::need(size_t n, const char* what) const {
+    if (n <= bytes) return ptr;
+    CUT_FAIL(CUT_E_INVAL,
+             "%s needs a work area of %zu bytes, %zu are reserved: call cut_graph_reserve with this shape "
+             "(and again after a tiling change that adds partial rows)",
+             what, n, bytes);
+}
+
+void Workspace::reserve(size_t n) {
+    if (n <= bytes) return;
+    if (ptr) {
+        HIP_CHECK(hipDeviceSynchronize());
+        (void)hipFree(ptr);
+        ptr = nullptr;
+        bytes = 0;
+    }
+    hipError_t e = hipMalloc(&ptr, n);
+    if (e != hipSuccess) {
+        ptr = nullptr;
+        (void)hipGetLastError();  // reported here, not by a later call
+        CUT_FAIL(CUT_E_NOMEM, "work area hipMalloc(%zu): %s", n, hipGetErrorString(e));
+    }
+    bytes = n;
+}
+
+void Workspace::reserve_optional(size_t n) {
+    if (n <= bytes) return;
+    size_t left = 0, total = 0;
+    void* p = nullptr;
+    if (hipMemGetInfo(&left, &total) != hipSuccess || n > left / 2 || hipMalloc(&p, n) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (ptr) {
+        const hipError_t e = hipDeviceSynchronize();
+        if (e != hipSuccess) {
+            (void)hipFree(p);
+            CUT_FAIL(CUT_E_DEVICE, "hipDeviceSynchronize: %s", hipGetErrorString(e));
+        }
+        (void)hipFree(ptr);
+    }
+    ptr = p;
+    bytes = n;
+}
+
+void Workspace::release() {
+    if (ptr) (void)hipFree(ptr);
+    ptr = nullptr;
+    bytes = 0;
+}
+
+void reserve_shape(Graph& g, int64_t nsets, int64_t nops, int64_t ckpt_every, uint32_t what, bool extra) {
     size_t part = 0, rows = 0, small = 0, deriv = 0, ws = 0;
     for (int prec = CUT_F64; prec <= CUT_F32; ++prec) {
         const size_t fwd = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec);
@@ -22,24 +73,18 @@ void reserve_shape(Graph& g, int64_t nsets, int64_t nops, int64_t ckpt_every, ui
     if (what & CUT_RESERVE_APPLY) small = sizeof(double) * 2 * g.N * nsets;
     if ((what & CUT_RESERVE_ADJOINT) && ckpt_every > 0)
         ws = std::max(ws, flow_ws_bytes(g, nsets, nops, CUT_F64, flow_adjoint_extra(g, nsets, nops, ckpt_every)));
-    if (what & CUT_RESERVE_APPLY) {
-        // the shared rows, if the memory is there: their actions run on the
-        // records without them
-        try {
-            g.rows.reserve(std::max(rows, outside_partial_bytes(g, nsets, nops)));
-        } catch (const Fail&) {
-        }
-    }
     g.ws_part.reserve(part);
     g.ws_small.reserve(small);
     g.ws_deriv.reserve(deriv);
     g.ws.reserve(ws);
+    // the shared rows: their actions run on the records without them
+    if (extra && (what & CUT_RESERVE_APPLY)) g.rows.reserve_optional(std::max(rows, outside_partial_bytes(g, nsets, nops)));
 }
 
-void SharedRows::reserve(size_t n) {
+void SharedRows::reserve_optional(size_t n) {
     std::lock_guard<std::mutex> lock(mu);
     if (n > 0 && !done) HIP_CHECK(hipEventCreateWithFlags(&done, hipEventDisableTiming));
-    ws.reserve(n);
+    ws.reserve_optional(n);
 }
 
 SharedUse::SharedUse(SharedRows& r_, size_t least, hipStream_t s_) : r(r_), lock(r_.mu), s(s_) {
@@ -65,7 +110,7 @@ void SharedRows::release() {
 }
 
 void rereserve(Graph& g) {
-    for (const auto& r : g.reserved) reserve_shape(g, r[0], r[1], r[2], (uint32_t)r[3]);
+    for (const auto& r : g.reserved) reserve_shape(g, r[0], r[1], r[2], (uint32_t)r[3], true);
 }
 
 }  // namespace cut
@@ -81,9 +126,11 @@ extern "C" cut_status cut_graph_reserve(cut_graph_t h, int64_t nsets, int64_t no
     if (ckpt_every < 0 || ((what & CUT_RESERVE_ADJOINT) && ckpt_every == 0))
         CUT_FAIL(CUT_E_INVAL, "cut_graph_reserve: CUT_RESERVE_ADJOINT needs ckpt_every > 0");
     DeviceGuard dg(g.device);
-    reserve_shape(g, nsets, nops, ckpt_every, what);
+    // memory that was short for a shape is not asked for again on each call
     const std::vector<int64_t> key = {nsets, nops, ckpt_every, (int64_t)what};
-    if (std::find(g.reserved.begin(), g.reserved.end(), key) == g.reserved.end()) g.reserved.push_back(key);
+    const bool known = std::find(g.reserved.begin(), g.reserved.end(), key) != g.reserved.end();
+    reserve_shape(g, nsets, nops, ckpt_every, what, !known);
+    if (!known) g.reserved.push_back(key);
     ABI_END
 }
 

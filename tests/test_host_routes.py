@@ -123,3 +123,27 @@ out([a, [k for k, _ in kernels(log())]])
 """)
     assert set(a) == set(b) == {"k_triples", "k_tri_combine"}
     assert b.count("k_triples") == launches
+
+
+def test_optional_rows_that_do_not_fit_cost_nothing():
+    """Short of memory for the outside-space partial rows of a larger shape: the reservation
+    succeeds, areas held before stay, no error is left behind and later calls do not try again."""
+    out = H.run("""
+g = graph(18, L.CUT_BUILD_OUTSIDE)
+L.cut_graph_reserve(g, 8, 3, 0, L.CUT_RESERVE_APPLY)
+held = L.cut_graph_reserved_bytes(g)
+fake.fake_limit(fake.fake_used() + (64 << 20))   # the larger shape's outside rows need 76 MiB
+log()
+L.cut_graph_reserve(g, 32, 4, 0, L.CUT_RESERVE_APPLY)
+first = log()
+L.cut_graph_reserve(g, 32, 4, 0, L.CUT_RESERVE_APPLY)
+again = log()
+a = lambda which, n, p: L.cut_graph_apply(g, which, L.CUT_F64, n, p, Buf(n), Buf(n * p), Buf(n * p), stream=0x11)
+a(2, 8, 3), a(0, 8, 3), a(2, 32, 4)
+out([held, L.cut_graph_reserved_bytes(g), first, again, [k for k, _ in kernels(log())]])
+""")
+    held, now, first, again, ks = out
+    assert now >= held and again == []
+    assert not any(l.startswith("free") and int(l.split()[1]) == 4 * 18564 * 24 * 8 for l in first)
+    assert ks[:2] == ["k_outside", "k_tri_combine"]
+    assert ks[-1] == "k_pass"   # the larger shape's action: not one of its operands fits
