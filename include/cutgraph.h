@@ -213,11 +213,7 @@ void cut_graph_free(cut_graph_t g);
  * coefficient sets and nops operands per set, in every precision, for the
  * call kinds in `what`:
  *   CUT_RESERVE_APPLY   cut_graph_apply (partial rows of chunked or tiled
- *                       forward passes and of the products in triple space;
- *                       for a graph with E_C also up to 2 GiB of partial rows
- *                       of the outside-space action, which runs without them,
- *                       slower, where twice that memory is not free when the
- *                       shape is first reserved) and cut_generator_vjp;
+ *                       forward passes) and cut_generator_vjp;
  *   CUT_RESERVE_FLOW    cut_flow_integrate (stage operands, RK accumulator,
  *                       generator, step counters; plus the outside-space
  *                       diagnostic buffers when the graph holds E_C);
@@ -225,6 +221,11 @@ void cut_graph_free(cut_graph_t g);
  *   CUT_RESERVE_ADJOINT cut_flow_adjoint with checkpoints every ckpt_every
  *                       steps (stage storage of one checkpoint block).
  * Work areas only grow; a reservation also covers every smaller nsets / nops.
+ * Where the shape's passes can run as products in triple space, every kind also
+ * reserves their partial rows (at 24 modes 0.4 MB a column, at 40 4 MB), and
+ * CUT_RESERVE_APPLY on a graph with E_C those of the outside-space action (up
+ * to 2 GiB): if twice that memory is free when the shape is first reserved; the
+ * calls run on the records, slower, without.
  * The shape is remembered: cut_graph_set_tiling and cut_graph_autotune
  * re-size the work areas for every shape reserved so far.  Growing
  * synchronises the device and moves the work area (captured flow step graphs

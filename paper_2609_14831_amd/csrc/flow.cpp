@@ -127,7 +127,7 @@ struct FlowLayout {
 static FlowLayout flow_layout(const Graph& g, int64_t nsets, int64_t nops, int prec, size_t extra) {
     const bool f32 = prec != CUT_F64;
     FlowLayout L{};
-    L.part_bytes = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec);
+    L.part_bytes = record_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec);
     const int64_t N = g.N, cols = nops * nsets;
     const size_t tb = f32 ? 4 : 8;
     size_t o = 0;
@@ -190,6 +190,11 @@ static FlowBufs flow_bufs(Graph& g, int64_t nsets, int64_t nops, int prec, size_
     f.flag = (int32_t*)(b + L.fl);
     f.part = L.part_bytes ? (double*)(b + L.part) : nullptr;
     f.part_bytes = L.part_bytes;
+    const size_t tri = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec);
+    if (tri > L.part_bytes && tri <= g.ws_tri.bytes) {
+        f.part = (double*)g.ws_tri.ptr;
+        f.part_bytes = tri;
+    }
     f.zp = (double*)(b + L.zp);
     f.perm = (int32_t*)(b + L.perm);
     if (extra_ptr) *extra_ptr = b + L.ex;
@@ -494,7 +499,7 @@ extern "C" cut_status cut_flow_integrate(cut_graph_t h, const cut_flow_params* p
         if (use_graph) {
             std::vector<uint64_t> key = {(uint64_t)(uintptr_t)zs, (uint64_t)(uintptr_t)g.ws.ptr, (uint64_t)p->generator,
                                          (uint64_t)p->precision, (uint64_t)nsets, (uint64_t)nops, 0, 0,
-                                         g.tiling_gen, (uint64_t)(uintptr_t)fb.part,
+                                         g.tiling_gen, (uint64_t)(uintptr_t)fb.part, (uint64_t)fb.part_bytes,
                                          (uint64_t)(uintptr_t)p->outside_norm2};
             std::memcpy(&key[6], &p->ds, 8);
             std::memcpy(&key[7], &p->delta, 8);

@@ -367,7 +367,8 @@ struct Graph {
     int64_t max_lds = 65536;         // LDS bytes one workgroup may allocate
     Workspace ws;                    // flow state and stage storage
     Workspace ws_small;              // scratch of single generator-VJP calls
-    Workspace ws_part;               // tile partial slots of single forward passes
+    Workspace ws_part;               // partial rows of single forward passes
+    Workspace ws_tri;                // partial rows of flows in triple space (none: their passes run on the records)
     Workspace ws_deriv;              // generator, tangent and float shadows of derivative calls
     SharedRows rows;                 // outside-space actions; forward actions without partial rows over the records
     // shapes reserved so far: (nsets, nops, ckpt_every, CUT_RESERVE_* flags)
@@ -473,7 +474,7 @@ double* forward_part(Graph& g, int32_t nsets, int32_t nops, int32_t precision, c
 // may take the route, and the pass  out = sign * sum_{r < nred} L(A_r) B_r
 // (A and B advance by nsets columns per r) with the epilogue of `a`
 void build_triples(Graph& g, const HostGraph& hg);
-size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops);
+size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops, int32_t precision);
 bool triples_usable(const Graph& g, const PassArgs& a);
 // the same for the outside-space action: `bytes` of partial rows at `part`, at
 // least outside_least() of them (more: more operands at a time)

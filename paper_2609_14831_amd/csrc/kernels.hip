@@ -1452,8 +1452,7 @@ size_t chunk_partial_bytes(const Graph& g, int32_t nsets, int32_t nops) {
 static bool quad_and_tiles(const Graph& g, int32_t nsets, int32_t nops, int32_t precision);
 
 size_t forward_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_t precision) {
-    const size_t b = record_partial_bytes(g, nsets, nops, precision);
-    return precision == CUT_F32 ? b : std::max(b, triples_partial_bytes(g, nsets, nops));
+    return std::max(record_partial_bytes(g, nsets, nops, precision), triples_partial_bytes(g, nsets, nops, precision));
 }
 
 double* forward_part(Graph& g, int32_t nsets, int32_t nops, int32_t precision, const char* what, size_t* bytes) {

@@ -58,27 +58,44 @@ void Workspace::release() {
     bytes = 0;
 }
 
+// Bytes of partial rows in triple space for the layout and every smaller number
+// of sets: fewer sets may be on the products' side of the line where more are not.
+static size_t triples_reserve_bytes(const Graph& g, int64_t nsets, int64_t nops, int prec) {
+    size_t b = triples_partial_bytes(g, nsets, nops, prec);
+    for (int64_t n : {32, 16, 8, 4, 1})
+        if (n < nsets) b = std::max(b, triples_partial_bytes(g, n, nops, prec));
+    return b;
+}
+
 void reserve_shape(Graph& g, int64_t nsets, int64_t nops, int64_t ckpt_every, uint32_t what, bool extra) {
-    size_t part = 0, rows = 0, small = 0, deriv = 0, ws = 0;
+    size_t part = 0, tri = 0, outside = 0, small = 0, deriv = 0, ws = 0;
+    bool area = false;  // whether the passes over the records keep partial rows
     for (int prec = CUT_F64; prec <= CUT_F32; ++prec) {
-        const size_t fwd = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec);
-        const bool area = record_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec) > 0;
-        if ((what & CUT_RESERVE_DERIV) || ((what & CUT_RESERVE_APPLY) && area)) part = std::max(part, fwd);
-        if ((what & CUT_RESERVE_APPLY) && !area) rows = std::max(rows, fwd);
+        const size_t rec = record_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec);
+        area = area || rec > 0;
+        if (what & (CUT_RESERVE_APPLY | CUT_RESERVE_DERIV)) part = std::max(part, rec);
+        if (extra) tri = std::max(tri, triples_reserve_bytes(g, nsets, nops, prec));
         if (what & CUT_RESERVE_DERIV)
             deriv = std::max({deriv, jvp_ws_bytes(g, nsets, nops, prec), vjp_ws_bytes(g, nsets, nops, prec)});
         if (what & CUT_RESERVE_FLOW)
             ws = std::max(ws, flow_ws_bytes(g, nsets, nops, prec, flow_outside_extra(g, nsets, nops)));
     }
-    if (what & CUT_RESERVE_APPLY) small = sizeof(double) * 2 * g.N * nsets;
+    if (what & CUT_RESERVE_APPLY) {
+        small = sizeof(double) * 2 * g.N * nsets;
+        outside = outside_partial_bytes(g, nsets, nops);
+    }
     if ((what & CUT_RESERVE_ADJOINT) && ckpt_every > 0)
         ws = std::max(ws, flow_ws_bytes(g, nsets, nops, CUT_F64, flow_adjoint_extra(g, nsets, nops, ckpt_every)));
     g.ws_part.reserve(part);
     g.ws_small.reserve(small);
     g.ws_deriv.reserve(deriv);
     g.ws.reserve(ws);
-    // the shared rows: their actions run on the records without them
-    if (extra && (what & CUT_RESERVE_APPLY)) g.rows.reserve_optional(std::max(rows, outside_partial_bytes(g, nsets, nops)));
+    if (!extra) return;
+    // partial rows of products: without them the same calls run on the records
+    const bool apply = (what & CUT_RESERVE_APPLY) != 0;
+    if (tri > 0 && ((apply && area) || (what & CUT_RESERVE_DERIV))) g.ws_part.reserve_optional(std::max(part, tri));
+    if (tri > 0 && (what & (CUT_RESERVE_FLOW | CUT_RESERVE_ADJOINT))) g.ws_tri.reserve_optional(std::max(part, tri));
+    if (apply) g.rows.reserve_optional(std::max(outside, area ? 0 : tri));
 }
 
 void SharedRows::reserve_optional(size_t n) {
@@ -138,6 +155,6 @@ extern "C" cut_status cut_graph_reserved_bytes(cut_graph_t h, int64_t* bytes) {
     ABI_BEGIN
     Graph& g = checked(h);
     if (!bytes) CUT_FAIL(CUT_E_INVAL, "cut_graph_reserved_bytes: null output");
-    *bytes = (int64_t)(g.ws.bytes + g.ws_small.bytes + g.ws_part.bytes + g.ws_deriv.bytes + g.rows.ws.bytes);
+    *bytes = (int64_t)(g.ws.bytes + g.ws_small.bytes + g.ws_part.bytes + g.ws_tri.bytes + g.ws_deriv.bytes + g.rows.ws.bytes);
     ABI_END
 }

@@ -319,9 +319,6 @@ static size_t tri_column_bytes(const Graph& g) {
     return (size_t)(4 * g.N + (int64_t)streams * g.tri.nq) * sizeof(double);
 }
 
-size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops) {
-    return g.tri.ok ? tri_column_bytes(g) * (size_t)(nops * nsets) : 0;
-}
 
 // Sets that decide a launch's shape: as wide as the segment kernel's lane
 // groups, at least min(8, nsets).
@@ -329,6 +326,10 @@ static int tri_width(const PassArgs& a) {
     const int w = a.s1 > 0 ? a.s1 - a.s0 : a.nsets;
     return std::max({w, std::min(8, (int)a.nsets), (int)a.gfloor});
 }
+
+// Whether the rows of a layout of ld elements a row are within reach of the
+// kernels' 32-bit byte offsets.
+static bool tri_reach(const Graph& g, int64_t ld, bool f64) { return g.N * ld * (f64 ? 8 : 4) < (int64_t)0x7FFFFFFF; }
 
 // FP64 and the compensated float modes (the sums are FP64 with exact products,
 // at least as accurate as either); 32-bit offsets into both operand arrays.
@@ -341,14 +342,24 @@ static int tri_width(const PassArgs& a) {
 //                   24 x 1 FP64 40 -> 31;  26 x 4 float 52 -> 52;  26 x 2 FP64 58 -> 53
 //   below it        20 x 8 FP64 0.96 of its speed, 24 x 16 float 0.97
 //                   with 5 operands  22 x 8 float 43 -> 56;  24 x 4 FP64 66 -> 71
+static bool tri_faster(const Graph& g, int w, bool f64) {
+    const int least = w > 32 ? kTriMinModes : f64 && w > 16 ? 20 : w == 1 || w > (f64 ? 4 : 16) ? 24 : 26;
+    return g.tri.m >= least;
+}
+
+// None where no pass over the layout is on the products' side of the line: their
+// widths are min(8, nsets) to nsets, and from there on the line falls with width.
+size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops, int32_t precision) {
+    const bool f64 = precision == CUT_F64;
+    if (!g.tri.ok || precision == CUT_F32 || !tri_reach(g, nops * nsets, f64)) return 0;
+    return tri_faster(g, (int)nsets, f64) ? tri_column_bytes(g) * (size_t)(nops * nsets) : 0;
+}
+
 bool triples_usable(const Graph& g, const PassArgs& a) {
     if (!g.tri.ok || a.precision == CUT_F32) return false;
     const bool f64 = a.precision == CUT_F64;
-    const int w = tri_width(a);
-    const int least = w > 32 ? kTriMinModes : f64 && w > 16 ? 20 : w == 1 || w > (f64 ? 4 : 16) ? 24 : 26;
-    if (g.tri.m < least) return false;
-    if (g.N * std::max({a.lda, a.ldb, a.ldfull}) * (f64 ? 8 : 4) >= (int64_t)0x7FFFFFFF) return false;
-    return a.part_bytes >= triples_partial_bytes(g, a.nsets, a.nops);
+    if (!tri_faster(g, tri_width(a), f64) || !tri_reach(g, std::max({a.lda, a.ldb, a.ldfull}), f64)) return false;
+    return a.part_bytes >= tri_column_bytes(g) * (size_t)((int64_t)a.nops * a.nsets);
 }
 
 void launch_triples(const Graph& g, int epi, const PassArgs& a, int nred, double sign, double* part, hipStream_t s) {

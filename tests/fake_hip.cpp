@@ -15,7 +15,7 @@
 
 static std::map<const void*, std::string> names;   // kernel stubs
 static std::map<char*, size_t> blocks;             // live allocations
-static size_t used = 0, limit = (size_t)288 << 30;
+static size_t used = 0, limit = (size_t)288 << 30, left = ~(size_t)0;
 static hipError_t last = hipSuccess;
 static std::string text;
 static std::set<void*> capturing;
@@ -41,6 +41,7 @@ const char* fake_log() { return text.c_str(); }
 void fake_clear() { text.clear(); }
 void fake_limit(size_t bytes) { limit = bytes; }
 size_t fake_used() { return used; }
+void fake_left(size_t bytes) { left = bytes; }
 void fake_capturing(void* stream, int on) {
     if (on) capturing.insert(stream);
     else capturing.erase(stream);
@@ -109,6 +110,7 @@ hipError_t hipFree(void* p) {
 }
 hipError_t hipMemGetInfo(size_t* f, size_t* t) {
     *f = limit > used ? limit - used : 0;
+    if (left < *f) *f = left;
     *t = limit;
     return hipSuccess;
 }

@@ -29,7 +29,7 @@ import ctypes as C, json, os, re, sys, types
 fake = C.CDLL({fake!r}, C.RTLD_GLOBAL)
 fake.fake_log.restype = C.c_char_p
 fake.fake_used.restype = C.c_size_t
-fake.fake_limit.argtypes = [C.c_size_t]
+fake.fake_limit.argtypes = fake.fake_left.argtypes = [C.c_size_t]
 fake.fake_capturing.argtypes = [C.c_void_p, C.c_int]
 fake.fake_block.argtypes, fake.fake_block.restype = [C.c_void_p], C.c_size_t
 sys.modules["torch"] = types.ModuleType("torch")   # the binding imports it for its runtime alone

@@ -147,3 +147,56 @@ out([held, L.cut_graph_reserved_bytes(g), first, again, [k for k, _ in kernels(l
     assert not any(l.startswith("free") and int(l.split()[1]) == 4 * 18564 * 24 * 8 for l in first)
     assert ks[:2] == ["k_outside", "k_tri_combine"]
     assert ks[-1] == "k_pass"   # the larger shape's action: not one of its operands fits
+
+
+APPLY, FLOW, DERIV, ADJOINT = 1, 2, 4, 8
+
+
+def _grown(m, nsets, nops, what):
+    """Bytes that a reservation on a fresh handle adds."""
+    return H.run(f"""
+g = graph({m}, load=L.CUT_LOAD_ADJOINT)
+L.cut_graph_reserve(g, {nsets}, {nops}, 4, {what})
+out(L.cut_graph_reserved_bytes(g))
+""")
+
+
+@pytest.mark.parametrize("what", [APPLY, FLOW, DERIV, ADJOINT])
+@pytest.mark.parametrize("m,nsets,nops", [(16, 32, 8), (22, 4, 5), (20, 40000, 3)])
+def test_no_rows_are_reserved_for_products_that_cannot_run(m, nsets, nops, what):
+    """Below the line at every width, or past the 2 GiB reach in every precision: no 4 N columns
+    of doubles beside what the records and the state need."""
+    n, cols = _strings(m), nsets * nops
+    state = {APPLY: 2 * n * nsets,                                # generator-VJP scratch
+             DERIV: n * (3 * nsets + 2 * cols),                   # generator, tangent and float shadows
+             FLOW: n * (4 * cols + 2 * nsets),                    # two operands, accumulator, ordered state
+             ADJOINT: n * ((4 + 17 + 4) * cols + 6 * nsets)}[what]
+    chunks = 4 * m * m * cols                                    # partial rows of the quadratic targets
+    assert _grown(m, nsets, nops, what) <= 8 * (state + chunks) * 1.05 + (1 << 20)
+
+
+def _strings(m):
+    return m * (m - 1) // 2 + m * (m - 1) * (m - 2) * (m - 3) // 24
+
+
+@pytest.mark.parametrize("short", [False, True])
+def test_products_give_way_where_their_rows_do_not_fit(short):
+    """Memory for the records' passes and the state but not for the products' rows: every call
+    that was reserved runs, on the records."""
+    ks = H.run(f"""
+g = graph(24, load=L.CUT_LOAD_ADJOINT)
+n, s, o = 10902, 8, 3
+if {short}:
+    fake.fake_left(1 << 20)   # what the runtime reports as free
+L.cut_graph_reserve(g, s, o, 0, L.CUT_RESERVE_APPLY)
+L.cut_graph_reserve(g, s, o, 0, L.CUT_RESERVE_DERIV)
+L.cut_graph_reserve(g, s, o, 0, L.CUT_RESERVE_FLOW)
+log()
+p = L.flow_params(L.CUT_GEN_G2, L.CUT_F64, 1e-3, flags=0, nonfinite=Buf(1))
+L.cut_flow_integrate(g, p, s, o, [2] * s, Buf(1), stream=0x11, reserve=False)
+L.cut_graph_apply(g, 0, L.CUT_F64, s, o, Buf(s), Buf(s * o), Buf(s * o), stream=0x11, reserve=False)
+L.cut_graph_vjp(g, L.CUT_GEN_G2, 0.5, L.CUT_F64, s, o, Buf(s), Buf(s * o), Buf(s * o), Buf(s), Buf(s * o), stream=0x11,
+                reserve=False)
+out([k for k, _ in kernels(log())])
+""")
+    assert ("k_pass" in ks) == short and ("k_triples" in ks) == (not short)
