@@ -502,9 +502,11 @@ cut_status cut_graph_set_tiling(cut_graph_t g, int64_t long_records, int64_t chu
  * CUT_F32X and `allow_other_float` != 0, over both compensated float modes;
  * applies the fastest tiling to the graph (a candidate must beat the best so
  * far, starting with the graph's current tiling, by at least 2 %) and returns
- * the choice.  Large Majorana passes (FP64, CUT_F32C, CUT_F32X) contract in
- * triple space and use no tiling: the graph's current one stays then.  It
- * allocates temporary operand buffers (zero-filled) and
+ * the choice.  Where all passes over the shape run as products in triple space
+ * (FP64, CUT_F32C and CUT_F32X from 26 modes, some widths from 24) there is
+ * no tiling to choose and the graph's current one stays; otherwise the passes
+ * over the records are timed, which a ragged flow's narrower passes may use
+ * also where its full width does not.  It allocates temporary operand buffers (zero-filled) and
  * synchronises the device.  Results are cached per (nsets, nops, precision,
  * allow_other_float).
  * Errors: CUT_E_INVAL, CUT_E_NOMEM, CUT_E_DEVICE. */

@@ -476,6 +476,8 @@ double* forward_part(Graph& g, int32_t nsets, int32_t nops, int32_t precision, c
 void build_triples(Graph& g, const HostGraph& hg);
 size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops, int32_t precision);
 bool triples_usable(const Graph& g, const PassArgs& a);
+// whether every pass over a layout runs in triple space, a flow's narrower ones too
+bool triples_always(const Graph& g, int64_t nsets, int64_t nops, int32_t precision);
 // the same for the outside-space action: `bytes` of partial rows at `part`, at
 // least outside_least() of them (more: more operands at a time)
 void build_outside(Graph& g, const HostGraph& hg);

@@ -355,6 +355,12 @@ size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops, int32_
     return tri_faster(g, (int)nsets, f64) ? tri_column_bytes(g) * (size_t)(nops * nsets) : 0;
 }
 
+bool triples_always(const Graph& g, int64_t nsets, int64_t nops, int32_t precision) {
+    const bool f64 = precision == CUT_F64;
+    if (!g.tri.ok || precision == CUT_F32 || !tri_reach(g, nops * nsets, f64)) return false;
+    return tri_faster(g, (int)std::min<int64_t>(8, nsets), f64);
+}
+
 bool triples_usable(const Graph& g, const PassArgs& a) {
     if (!g.tri.ok || a.precision == CUT_F32) return false;
     const bool f64 = a.precision == CUT_F64;

@@ -32,7 +32,7 @@ struct DevBuf {
 };
 
 double time_pass(Graph& g, int prec, int32_t nsets, int32_t nops, const void* eta, const void* x, double* y,
-                 double* partials, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+                 double* partials, size_t part_bytes, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     PassArgs p{};
     p.csr = &g.csr[0][0];
     p.A = eta;
@@ -45,7 +45,7 @@ double time_pass(Graph& g, int prec, int32_t nsets, int32_t nops, const void* et
     p.y = y;
     p.ldy = (int64_t)nops * nsets;
     p.scale = 1.0;
-    p.part_bytes = forward_partial_bytes(g, nsets, nops, prec);
+    p.part_bytes = part_bytes;
     for (int w = 0; w < 2; ++w) launch_forward(g, EPI_Y, p, partials, s);  // warm
     const int reps = 3;
     HIP_CHECK(hipEventRecord(e0, s));
@@ -85,8 +85,13 @@ extern "C" cut_status cut_graph_autotune(cut_graph_t h, int64_t nsets, int64_t n
         DevBuf eta(g.NG * nsets * tb), x(g.N * nsets * nops * tb), y(g.N * nsets * nops * 8);
         std::unique_ptr<DevBuf> part;
         size_t part_bytes = 0;
+        // where every pass runs in triple space there is no tiling to choose, the
+        // current one stays; a ragged flow's narrower passes may be on the records
+        // where its full width is not, and take the tiling that is best for it
+        const bool tiled = !triples_always(g, nsets, nops, precision);
         auto partials = [&](int pr) -> double* {
-            const size_t need = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, pr);
+            const size_t need = tiled ? record_partial_bytes(g, (int32_t)nsets, (int32_t)nops, pr)
+                                      : forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, pr);
             if (need == 0) return nullptr;
             if (!part || need > part_bytes) {
                 part.reset();
@@ -115,15 +120,6 @@ extern "C" cut_status cut_graph_autotune(cut_graph_t h, int64_t nsets, int64_t n
         const uint32_t shapes[] = {0u, CUT_TILE_TRIPLE_CHUNKS, CUT_TILE_NO_CHUNKS, CUT_TILE_TRIPLES,
                                    CUT_TILE_QUAD_BLOCKS, CUT_TILE_QUAD_BLOCKS | CUT_TILE_TRIPLE_CHUNKS,
                                    CUT_TILE_QUAD_BLOCKS | CUT_TILE_TRIPLES};
-        // passes in triple space have no tiling to choose: the current one stays
-        PassArgs probe{};
-        probe.precision = precision;
-        probe.nsets = (int32_t)nsets;
-        probe.nops = (int32_t)nops;
-        probe.lda = nsets;
-        probe.ldb = nops * nsets;
-        probe.part_bytes = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, precision);
-        const bool tiled = !triples_usable(g, probe);
         for (int64_t cr : crs)
             for (uint32_t xr = 0; tiled && xr <= 1; ++xr)
                 for (uint32_t shape : shapes) {
@@ -135,11 +131,16 @@ extern "C" cut_status cut_graph_autotune(cut_graph_t h, int64_t nsets, int64_t n
                     const uint32_t flags = (xr ? CUT_TILE_XCD_REMAP : 0u) | shape;
                     for (int pr : precs) cands.push_back({lr, cr, flags, pr, {0, 0, 0}});
                 }
+        auto time = [&](Cand& c, int round) {
+            double* rows = partials(c.prec);
+            // no bytes for products: the passes over the records
+            c.ms[round] = time_pass(g, c.prec, (int32_t)nsets, (int32_t)nops, eta.p, x.p, (double*)y.p, rows,
+                                    tiled ? 0 : part_bytes, s, e0, e1);
+        };
         for (int round = 0; round < 3; ++round)
             for (Cand& c : cands) {
                 apply_tiling(g, c.lr, c.cr, c.flags);
-                c.ms[round] = time_pass(g, c.prec, (int32_t)nsets, (int32_t)nops, eta.p, x.p, (double*)y.p,
-                                        partials(c.prec), s, e0, e1);
+                time(c, round);
             }
         auto median = [](const double* v) { return std::max(std::min(v[0], v[1]), std::min(std::max(v[0], v[1]), v[2])); };
         const Cand& c0 = cands[0];
@@ -173,8 +174,7 @@ extern "C" cut_status cut_graph_autotune(cut_graph_t h, int64_t nsets, int64_t n
         for (int round = 0; round < 3; ++round)
             for (Cand& c : bc) {
                 apply_tiling(g, c.lr, c.cr, c.flags);
-                c.ms[round] = time_pass(g, c.prec, (int32_t)nsets, (int32_t)nops, eta.p, x.p, (double*)y.p,
-                                        partials(c.prec), s, e0, e1);
+                time(c, round);
             }
         pick(bc, 0);
         apply_tiling(g, best.long_records, best.chunk_records, best.tiling_flags);

@@ -200,3 +200,20 @@ L.cut_graph_vjp(g, L.CUT_GEN_G2, 0.5, L.CUT_F64, s, o, Buf(s), Buf(s * o), Buf(s
 out([k for k, _ in kernels(log())])
 """)
     assert ("k_pass" in ks) == short and ("k_triples" in ks) == (not short)
+
+
+@pytest.mark.parametrize("m,nsets,prec,tuned", [(24, 40, "F32X", True), (20, 24, "F64", True), (24, 24, "F64", False),
+                                                (26, 40, "F32X", False)])
+def test_autotune_where_narrower_passes_run_on_the_records(m, nsets, prec, tuned):
+    """The full width runs in triple space in all four.  A ragged flow of the first two ends on the
+    records (below 24 or 26 modes), so their tiling is chosen by timed passes over the records."""
+    ks = H.run(f"""
+g = graph({m})
+log()
+L.cut_graph_autotune(g, {nsets}, 3, L.CUT_{prec}, 0)
+out([k for k, _ in kernels(log())])
+""")
+    assert ("k_triples" in ks) == (not tuned) and (ks.count("k_pass") > 40) == tuned
+    steps = f"[4] * 2 + [1] * {nsets - 2}"
+    flow = set(_flow_passes(m, nsets, 3, steps, prec))
+    assert flow == ({"k_triples", "k_pass"} if tuned else {"k_triples"})
