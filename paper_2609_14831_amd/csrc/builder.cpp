@@ -59,6 +59,18 @@ static uint64_t chunk_hash(const uint8_t* p, uint64_t n, uint64_t seed) {
     return mix64(h);
 }
 
+void run_threads(int n, const std::function<void()>& work) {
+    std::vector<std::thread> th;
+    th.reserve((size_t)std::max(1, n));
+    try {
+        for (int t = 1; t < n; ++t) th.emplace_back(work);
+    } catch (const std::system_error&) {
+        // no more threads: those there are share the work
+    }
+    work();
+    for (auto& t : th) t.join();
+}
+
 uint64_t checksum64(const void* data, uint64_t bytes) {
     const uint64_t C = 1ull << 20;
     const uint64_t nchunk = (bytes + C - 1) / C;
@@ -71,10 +83,7 @@ uint64_t checksum64(const void* data, uint64_t bytes) {
             dig[c] = chunk_hash((const uint8_t*)data + b, n, c);
         }
     };
-    std::vector<std::thread> th;
-    for (unsigned t = 1; t < nt && nchunk > 1; ++t) th.emplace_back(work);
-    work();
-    for (auto& t : th) t.join();
+    run_threads(nchunk > 1 ? (int)nt : 1, work);
     uint64_t h = 0x243f6a8885a308d3ull ^ bytes;
     for (uint64_t d : dig) h = mix64(h ^ d) + 0x9e3779b97f4a7c15ull;
     return h;
@@ -300,7 +309,7 @@ struct Algebra {
 // ---------------------------------------------------------------- writer ----
 static uint64_t align64(uint64_t x) { return (x + 63) & ~uint64_t(63); }
 
-static void parallel_for(int64_t n, int threads, const std::function<void(int64_t, int64_t)>& fn) {
+void parallel_for(int64_t n, int threads, const std::function<void(int64_t, int64_t)>& fn) {
     int nt = std::max(1, threads);
     if (n < 4096 || nt == 1) {
         fn(0, n);
@@ -311,10 +320,7 @@ static void parallel_for(int64_t n, int threads, const std::function<void(int64_
     auto work = [&]() {
         for (int64_t b; (b = next.fetch_add(blk)) < n;) fn(b, std::min(n, b + blk));
     };
-    std::vector<std::thread> th;
-    for (int t = 1; t < nt; ++t) th.emplace_back(work);
-    work();
-    for (auto& t : th) t.join();
+    run_threads(nt, work);
 }
 
 

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <functional>
 #include <mutex>
 #include <new>
 #include <string>
@@ -110,6 +111,12 @@ struct BundleHeader {
 static_assert(sizeof(BundleHeader) == 256, "header must be 256 bytes");
 
 uint64_t checksum64(const void* data, uint64_t bytes);
+
+// `work` on n threads, the calling one among them; fewer where they cannot be
+// started.  `work` must not throw and shares its items out by itself.
+void run_threads(int n, const std::function<void()>& work);
+// fn over [0, n) in blocks of 512
+void parallel_for(int64_t n, int threads, const std::function<void(int64_t, int64_t)>& fn);
 
 // host-side view of a bundle (owned vectors or a mapped file)
 struct HostGraph {

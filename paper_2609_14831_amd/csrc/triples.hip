@@ -111,17 +111,7 @@ void build_triples(Graph& g, const HostGraph& hg) {
             if (!ok) good = false;
         }
     };
-    const int nth = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-    std::vector<std::thread> th;
-    int64_t k0 = 0;
-    for (int t = 0; t < nth; ++t) {
-        // pieces of about equal record counts
-        const int64_t goal = off[N] / nth * (t + 1);
-        const int64_t k1 = t == nth - 1 ? N : std::lower_bound(off + k0, off + N, goal) - off;
-        th.emplace_back(check, k0, k1);
-        k0 = k1;
-    }
-    for (auto& t : th) t.join();
+    parallel_for(N, (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency())), check);
     if (!good) return;
     const int64_t ntau = nt + m;
     const int64_t ntp = ntau + 16;

@@ -6,12 +6,15 @@
 #include <hip/hip_runtime_api.h>
 #include <sys/mman.h>
 
+#include <dlfcn.h>
+
 #include <cstdio>
 #include <cstring>
 #include <cxxabi.h>
 #include <map>
 #include <set>
 #include <string>
+#include <system_error>
 
 static std::map<const void*, std::string> names;   // kernel stubs
 static std::map<char*, size_t> blocks;             // live allocations
@@ -50,6 +53,17 @@ void fake_capturing(void* stream, int on) {
 size_t fake_block(void* p) {
     auto it = blocks.find((char*)p);
     return it == blocks.end() ? 0 : it->second;
+}
+
+// threads that may still be started (< 0: any number)
+static int threads_left = -1;
+void fake_threads(int n) { threads_left = n; }
+#define THREAD_START "_ZNSt6thread15_M_start_threadESt10unique_ptrINS_6_StateESt14default_deleteIS1_EEPFvvE"
+void fake_start_thread(void* self, void* state, void (*depend)()) asm(THREAD_START);
+void fake_start_thread(void* self, void* state, void (*depend)()) {
+    if (threads_left == 0) throw std::system_error(EAGAIN, std::generic_category(), "no thread");
+    if (threads_left > 0) --threads_left;
+    ((void (*)(void*, void*, void (*)()))dlsym(RTLD_NEXT, THREAD_START))(self, state, depend);
 }
 
 // ------------------------------------------------------------- registration --

@@ -217,3 +217,20 @@ out([k for k, _ in kernels(log())])
     steps = f"[4] * 2 + [1] * {nsets - 2}"
     flow = set(_flow_passes(m, nsets, 3, steps, prec))
     assert flow == ({"k_triples", "k_pass"} if tuned else {"k_triples"})
+
+
+@pytest.mark.parametrize("threads", [0, 1])
+def test_load_without_threads(threads):
+    """The checks at load run in the calling thread where none can be started."""
+    ks = H.run(f"""
+import tempfile
+with tempfile.TemporaryDirectory() as d:
+    path = os.path.join(d, "g.cgb")
+    L.cut_graph_build(L.CUT_ALG_MAJORANA, 26, path, 0, 0)
+    fake.fake_threads({threads})
+    g = L.cut_graph_load(path, 0, 0)
+fake.fake_threads(-1)
+L.cut_graph_apply(g, 0, L.CUT_F64, 4, 1, Buf(4), Buf(4), Buf(4), stream=0x11)
+out([k for k, _ in kernels(log())])
+""")
+    assert ks == ["k_triples", "k_tri_combine"]
