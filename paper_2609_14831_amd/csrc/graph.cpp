@@ -1079,8 +1079,24 @@ extern "C" cut_status cut_graph_load(const char* path, int32_t dev, uint32_t fla
                 g->max_lds = lds;
         }
         if (!pb) build_tiles(*g, hg, code);
-        build_triples(*g, hg);
-        build_outside(*g, hg);
+        // products in triple space: where memory for their tables is short, the
+        // graph runs on its records
+        try {
+            build_triples(*g, hg);
+        } catch (const Fail& f) {
+            if (f.st != CUT_E_NOMEM) throw;
+            g->tri.release();
+        } catch (const std::bad_alloc&) {
+            g->tri.release();
+        }
+        try {
+            build_outside(*g, hg);
+        } catch (const Fail& f) {
+            if (f.st != CUT_E_NOMEM) throw;
+            g->tri.release_outside();
+        } catch (const std::bad_alloc&) {
+            g->tri.release_outside();
+        }
         HIP_CHECK(hipDeviceSynchronize());
         HIP_CHECK(hipSetDevice(prev));
         *out = (cut_graph_t)g;

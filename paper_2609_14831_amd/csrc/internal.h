@@ -277,6 +277,7 @@ struct TriPlan {
     int4* tasks = nullptr;
     int32_t task0[4] = {0, 0, 0, 0};
     void release();
+    void release_outside();
 };
 
 // Device work area of a graph handle.  It is sized only by reservation calls

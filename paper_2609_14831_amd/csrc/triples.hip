@@ -21,17 +21,23 @@
 
 namespace cut {
 
-void TriPlan::release() {
-    if (tab) (void)hipFree(tab);
-    if (tmask) (void)hipFree(tmask);
+void TriPlan::release_outside() {
     if (bin) (void)hipFree(bin);
     if (pair2) (void)hipFree(pair2);
     if (tri3) (void)hipFree(tri3);
     if (tasks) (void)hipFree(tasks);
-    tab = bin = pair2 = tri3 = nullptr;
-    tmask = nullptr;
+    bin = pair2 = tri3 = nullptr;
     tasks = nullptr;
-    ok = out_ok = false;
+    out_ok = false;
+}
+
+void TriPlan::release() {
+    release_outside();
+    if (tab) (void)hipFree(tab);
+    if (tmask) (void)hipFree(tmask);
+    tab = nullptr;
+    tmask = nullptr;
+    ok = false;
 }
 
 static inline int above(uint64_t set, int q) { return __builtin_popcountll(set & ~((2ull << q) - 1)) & 1; }
@@ -62,12 +68,16 @@ static int record_sign(uint64_t K, uint64_t I, uint64_t J) {
     return 0;
 }
 
-static void* upload(const void* src, size_t bytes) {
-    void* d = nullptr;
-    const hipError_t e = hipMalloc(&d, bytes);
-    if (e != hipSuccess) CUT_FAIL(CUT_E_NOMEM, "hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e));
-    HIP_CHECK(hipMemcpy(d, src, bytes, hipMemcpyHostToDevice));
-    return d;
+// device copy of a host array in *dst, which its owner frees
+template <class T>
+static void upload(T** dst, const T* src, size_t count) {
+    const hipError_t e = hipMalloc((void**)dst, count * sizeof(T));
+    if (e != hipSuccess) {
+        *dst = nullptr;
+        (void)hipGetLastError();  // reported here, not by a later call
+        CUT_FAIL(CUT_E_NOMEM, "hipMalloc(%zu bytes): %s", count * sizeof(T), hipGetErrorString(e));
+    }
+    HIP_CHECK(hipMemcpy(*dst, src, count * sizeof(T), hipMemcpyHostToDevice));
 }
 
 // modes below which no width is faster in triple space
@@ -133,8 +143,8 @@ void build_triples(Graph& g, const HostGraph& hg) {
     p.ntau = (int32_t)ntau;
     p.ntp = (int32_t)ntp;
     p.c = (double)c0;
-    p.tab = (uint32_t*)upload(tab.data(), tab.size() * 4);
-    p.tmask = (uint64_t*)upload(tau.data(), (size_t)nt * 8);
+    upload(&p.tab, tab.data(), tab.size());
+    upload(&p.tmask, tau.data(), (size_t)nt);
     p.ok = true;
 }
 
@@ -540,7 +550,8 @@ void build_outside(Graph& g, const HostGraph& hg) {
     TriPlan& p = g.tri;
     const int64_t n = g.n_out;
     const int m = p.m;
-    if (!p.ok || !g.have_outside || m < kOutMinModes || hg.off[2][1] == hg.off[2][0]) return;
+    p.release_outside();
+    if (!p.ok || !g.have_outside || m < kOutMinModes || n < 1 || hg.off[2][1] == hg.off[2][0]) return;
     std::vector<uint32_t> bin(7 * 64);
     for (int k = 0; k < 7; ++k)
         for (int c = 0; c < 64; ++c) {
@@ -575,10 +586,10 @@ void build_outside(Graph& g, const HostGraph& hg) {
             }
         p.task0[w + 1] = (int32_t)tasks.size();
     }
-    p.bin = (uint32_t*)upload(bin.data(), bin.size() * 4);
-    p.pair2 = (uint32_t*)upload(pair2.data(), pair2.size() * 4);
-    p.tri3 = (uint32_t*)upload(tri3.data(), tri3.size() * 4);
-    p.tasks = (int4*)upload(tasks.data(), tasks.size() * sizeof(int4));
+    upload(&p.bin, bin.data(), bin.size());
+    upload(&p.pair2, pair2.data(), pair2.size());
+    upload(&p.tri3, tri3.data(), tri3.size());
+    upload(&p.tasks, tasks.data(), tasks.size());
     // the factor of the first record, the others against it
     const uint64_t Q0 = hg.out_labels[0];
     const uint64_t I = hg.labels[hg.ri[2][0]], J = hg.labels[hg.rj[2][0]], both = I & J, U = I & ~both, V = J & ~both;
@@ -587,17 +598,22 @@ void build_outside(Graph& g, const HostGraph& hg) {
     inv += __builtin_popcountll(U & ~(both - 1)) + __builtin_popcountll(V & ~(both - 1));
     if ((U ^ V) != Q0 || __builtin_popcountll(both) != 1) return;
     p.cout = (inv & 1) ? -(double)hg.rc[2][0] : (double)hg.rc[2][0];
-    uint64_t* dl = (uint64_t*)upload(hg.labels, (size_t)g.N * 8);
-    uint64_t* dol = (uint64_t*)upload(hg.out_labels, (size_t)n * 8);
+    struct Temp {
+        uint64_t *labels = nullptr, *out = nullptr;
+        int32_t* bad = nullptr;
+        ~Temp() {
+            (void)hipFree(labels);
+            (void)hipFree(out);
+            (void)hipFree(bad);
+        }
+    } d;
     int32_t bad = 0;
-    int32_t* dbad = (int32_t*)upload(&bad, 4);
-    hipLaunchKernelGGL(k_check_outside, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, 0, n, m, p.bin, dl, dol,
-                       g.csr[2][0].off, g.csr[2][0].rec, p.cout, dbad);
-    const hipError_t e = hipMemcpy(&bad, dbad, 4, hipMemcpyDeviceToHost);
-    (void)hipFree(dl);
-    (void)hipFree(dol);
-    (void)hipFree(dbad);
-    HIP_CHECK(e);
+    upload(&d.labels, hg.labels, (size_t)g.N);
+    upload(&d.out, hg.out_labels, (size_t)n);
+    upload(&d.bad, &bad, 1);
+    hipLaunchKernelGGL(k_check_outside, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, 0, n, m, p.bin, d.labels, d.out,
+                       g.csr[2][0].off, g.csr[2][0].rec, p.cout, d.bad);
+    HIP_CHECK(hipMemcpy(&bad, d.bad, 4, hipMemcpyDeviceToHost));
     p.out_ok = p.cout != 0.0 && !bad;
 }
 

@@ -234,3 +234,39 @@ L.cut_graph_apply(g, 0, L.CUT_F64, 4, 1, Buf(4), Buf(4), Buf(4), stream=0x11)
 out([k for k, _ in kernels(log())])
 """)
     assert ks == ["k_triples", "k_tri_combine"]
+
+
+def test_load_where_the_products_tables_do_not_fit():
+    """Short of memory at any of the tables' allocations the graph loads and runs on its records;
+    nothing is lost."""
+    out = H.run("""
+import tempfile
+with tempfile.TemporaryDirectory() as d:
+    path = os.path.join(d, "g.cgb")
+    L.cut_graph_build(L.CUT_ALG_MAJORANA, 20, path, 0, L.CUT_BUILD_OUTSIDE)
+    log()
+    g = L.cut_graph_load(path, 0, 0)
+    used, before = 0, []   # bytes held before each allocation, and its size
+    for l in log():
+        if l.startswith("malloc"):
+            before.append((used, int(l.split()[1])))
+            used += before[-1][1]
+        elif l.startswith("free"):
+            used -= int(l.split()[1])
+    L.cut_graph_free(g)
+    res = []
+    for held, size in before[-9:]:   # two tables, four of the outside space, three of its check
+        fake.fake_limit(fake.fake_used() + held + size - 1)
+        g = L.cut_graph_load(path, 0, 0)
+        fake.fake_limit(288 << 30)
+        log()
+        for which in (0, 2):
+            L.cut_graph_apply(g, which, L.CUT_F64, 20, 1, Buf(20), Buf(20), Buf(20), stream=0x11)
+        res.append([k for k, _ in kernels(log())])
+        L.cut_graph_free(g)
+    out([res, fake.fake_used()])
+""")
+    res, left = out
+    assert left == 0
+    for k, ks in enumerate(res):
+        assert ("k_triples" in ks) == (k >= 2) and "k_outside" not in ks, (k, ks)
