@@ -3,6 +3,7 @@ kernels a call launches, in which order its streams are put, and what it
 allocates."""
 import pytest
 
+import flow_routes as FR
 import host_runtime as H
 
 
@@ -85,10 +86,10 @@ out(log())
     assert [l.split(" ", 3)[3].split("<")[0] for l in out] == ["k_pass"], out
 
 
-def _flow_passes(m, nsets, nops, steps, prec, tiling=None):
+def _flow_passes(m, nsets, nops, steps, prec, tiling=None, outside=False):
     """The kernels over E_L (segment, chunk and triple-space passes) of a flow, in order."""
     lines = H.run(f"""
-g = graph({m})
+g = graph({m}, L.CUT_BUILD_OUTSIDE if {outside} else 0)
 {"L.cut_graph_set_tiling(g, *" + repr(tiling) + ")" if tiling else ""}
 L.cut_graph_reserve(g, {nsets}, {nops}, 0, L.CUT_RESERVE_FLOW)
 log()
@@ -270,3 +271,9 @@ with tempfile.TemporaryDirectory() as d:
     assert left == 0
     for k, ks in enumerate(res):
         assert ("k_triples" in ks) == (k >= 2) and "k_outside" not in ks, (k, ks)
+
+
+@pytest.mark.parametrize("m,nsets,nops,outside,prec,tiling,kernels", FR.RECORDS + FR.TRIPLES + FR.SMALL)
+def test_flows_run_the_kernels_they_are_tested_for(m, nsets, nops, outside, prec, tiling, kernels):
+    ks = _flow_passes(m, nsets, nops, FR.steps(nsets), prec, tiling, outside)
+    assert set(ks) == kernels, sorted(set(ks))
