@@ -188,6 +188,17 @@ __global__ __launch_bounds__(kSmallThreads) void k_flow_small(SmallFlow a) {
 //   12 modes (48840), 64 x 1 117 -> 54, 64 x 5 float 151 -> 97; but 1 x 1 48 -> 53, 4 x 5 68 -> 95
 constexpr int64_t kSmallRecords = 20000, kSmallRecordsWide = 60000;
 
+// Sets up to which it is: two workgroups are resident per CU, so past 512 sets its
+// time grows with their number, while a launch over the card is not yet full.  An
+// 8-step call, ms, launches -> here (G2; 12 modes in float have the wide graphs' line):
+//   up to it   8 modes, 2048 sets float 0.82 -> 0.78, FP64 0.98 -> 0.79; 6 modes, 2048 float 0.58 -> 0.51
+//              12 modes, 1536 sets x 2 operands float 3.18 -> 3.06; 8 x 8 one-body, 2048 sets 0.62 -> 0.47
+//   past it    8 modes, 4096 sets float 1.27 -> 1.52; 12 modes, 4096 float 5.57 -> 6.57, 2048 x 2 3.82 -> 4.06
+//              16 x 16 one-body, 4096 sets 2.25 -> 2.43
+// FP64 record passes have half the rate: there the longer graphs of G2 have no such
+// line (12,000 sets: 10 modes 10.2 -> 7.3, 12 modes 21.0 -> 19.1 and x 5 81.5 -> 35.3).
+constexpr int64_t kSmallSets = 2048, kSmallSetsWide = 1536, kSmallLongRecords = 10000;
+
 static int64_t small_lds_bytes(const Graph& g, int gen, int64_t nops, bool records) {
     int64_t b = (g.N * (4 * nops + 1) + g.NG) * 8 + (g.N + g.NG + 3) / 2 * 8;
     if (records) b += (g.csr[0][0].nrec + (gen == CUT_GEN_G2 ? 0 : g.csr[1][0].nrec)) * 8;
@@ -200,7 +211,10 @@ static int64_t small_lds_bytes(const Graph& g, int gen, int64_t nops, bool recor
 bool small_flow_usable(const Graph& g, int gen, int prec, int64_t nsets, int64_t nops) {
     if (prec == CUT_F32 || (gen != CUT_GEN_WEGNER_GRAPH && gen != CUT_GEN_G2) || nops > 8) return false;
     if (g.have_outside || g.csr[0][0].cx || g.NG != g.N) return false;
-    return g.csr[0][0].nrec <= (nsets > 32 ? kSmallRecordsWide : kSmallRecords) &&
+    const int64_t nrec = g.csr[0][0].nrec;
+    const bool any = prec == CUT_F64 && gen == CUT_GEN_G2 && nrec > kSmallLongRecords;
+    if (!any && nsets > (nrec > kSmallRecords ? kSmallSetsWide : kSmallSets)) return false;
+    return nrec <= (nsets > 32 ? kSmallRecordsWide : kSmallRecords) &&
            small_lds_bytes(g, gen, nops, false) <= g.max_lds;
 }
 

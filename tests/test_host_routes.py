@@ -277,3 +277,18 @@ with tempfile.TemporaryDirectory() as d:
 def test_flows_run_the_kernels_they_are_tested_for(m, nsets, nops, outside, prec, tiling, kernels):
     ks = _flow_passes(m, nsets, nops, FR.steps(nsets), prec, tiling, outside)
     assert set(ks) == kernels, sorted(set(ks))
+
+
+@pytest.mark.parametrize("m,nsets,prec,small", [(8, 2048, "F32X", True), (8, 2049, "F32X", False), (8, 2049, "F64", False),
+                                                (12, 1536, "F32X", True), (12, 1537, "F32X", False),
+                                                (10, 2049, "F32X", False), (10, 5000, "F64", True), (12, 5000, "F64", True)])
+def test_one_launch_flows_up_to_the_sets_where_they_are_faster(m, nsets, prec, small):
+    ks = H.run(f"""
+g = graph({m})
+L.cut_graph_reserve(g, {nsets}, 1, 0, L.CUT_RESERVE_FLOW)
+log()
+p = L.flow_params(L.CUT_GEN_G2, L.CUT_{prec}, 1e-3, flags=0, nonfinite=Buf(1))
+L.cut_flow_integrate(g, p, {nsets}, 1, [2] * {nsets}, Buf(1), stream=0x11, reserve=False)
+out([k for k, _ in kernels(log())])
+""")
+    assert ("k_flow_small" in ks) == small and ("k_pass" in ks) == (not small)
