@@ -176,7 +176,8 @@ size_t flow_adjoint_extra(const Graph& g, int64_t nsets, int64_t nops, int64_t c
     return al(nslot * M * 8) + 4 * al(M * 8) + 2 * al(g.NG * nsets * 8) + al(2 * g.N * nsets * 8);
 }
 
-static FlowBufs flow_bufs(Graph& g, int64_t nsets, int64_t nops, int prec, size_t extra, char** extra_ptr) {
+static FlowBufs flow_bufs(Graph& g, int64_t nsets, int64_t nops, int prec, size_t extra, char** extra_ptr,
+                          bool adjoint = false) {
     const FlowLayout L = flow_layout(g, nsets, nops, prec, extra);
     char* b = (char*)g.ws.need(L.total, extra > 0 ? "the flow (with its diagnostic or adjoint storage)" : "the flow");
     FlowBufs f;
@@ -190,7 +191,7 @@ static FlowBufs flow_bufs(Graph& g, int64_t nsets, int64_t nops, int prec, size_
     f.flag = (int32_t*)(b + L.fl);
     f.part = L.part_bytes ? (double*)(b + L.part) : nullptr;
     f.part_bytes = L.part_bytes;
-    const size_t tri = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec);
+    const size_t tri = forward_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec, adjoint);
     if (tri > L.part_bytes && tri <= g.ws_tri.bytes) {
         f.part = (double*)g.ws_tri.ptr;
         f.part_bytes = tri;
@@ -655,7 +656,7 @@ extern "C" cut_status cut_flow_adjoint(cut_graph_t h, const cut_flow_params* p, 
         const int64_t nslot = (int64_t)C * 4 + 1;
         const size_t extra = flow_adjoint_extra(g, nsets, nops, C);
         char* ex = nullptr;
-        FlowBufs fb = flow_bufs(g, nsets, nops, CUT_F64, extra, &ex);
+        FlowBufs fb = flow_bufs(g, nsets, nops, CUT_F64, extra, &ex, true);
         double* St = (double*)ex;
         ex += al(nslot * M * 8);
         double* zr = (double*)ex;

@@ -464,7 +464,8 @@ bool tiles_usable(const Graph& g, int32_t nsets, int32_t nops, int32_t precision
 // bytes of partial rows the chunked forward pass needs (0: not chunked)
 size_t chunk_partial_bytes(const Graph& g, int32_t nsets, int32_t nops);
 // partial work area a forward pass of record set 0 needs (tiles or chunks)
-size_t forward_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_t precision);
+// (transposed: with the transposed actions in triple space too)
+size_t forward_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_t precision, bool transposed = false);
 size_t tile_partial_bytes(const Graph& g, int32_t nsets, int32_t nops);
 bool quadblocks_usable(const Graph& g, int32_t nsets, int32_t nops, int32_t precision);
 void launch_forward(const Graph& g, int epi, const PassArgs& a, double* partials, hipStream_t s);
@@ -475,14 +476,14 @@ size_t record_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_t
 
 // the partial rows of a pass outside flows: the reserved area when it holds
 // every route's, else what the records alone need (`what` names the call that
-// fails without them; null: the call runs without partial rows then)
+// fails without them; null: a VJP, which runs without partial rows then)
 double* forward_part(Graph& g, int32_t nsets, int32_t nops, int32_t precision, const char* what, size_t* bytes);
 
 // triple-space passes of Majorana graphs: plan, partial rows, whether a pass
 // may take the route, and the pass  out = sign * sum_{r < nred} L(A_r) B_r
 // (A and B advance by nsets columns per r) with the epilogue of `a`
 void build_triples(Graph& g, const HostGraph& hg);
-size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops, int32_t precision);
+size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops, int32_t precision, bool transposed);
 bool triples_usable(const Graph& g, const PassArgs& a);
 // whether every pass over a layout runs in triple space, a flow's narrower ones too
 bool triples_always(const Graph& g, int64_t nsets, int64_t nops, int32_t precision);

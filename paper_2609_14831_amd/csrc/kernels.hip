@@ -1451,12 +1451,13 @@ size_t chunk_partial_bytes(const Graph& g, int32_t nsets, int32_t nops) {
 
 static bool quad_and_tiles(const Graph& g, int32_t nsets, int32_t nops, int32_t precision);
 
-size_t forward_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_t precision) {
-    return std::max(record_partial_bytes(g, nsets, nops, precision), triples_partial_bytes(g, nsets, nops, precision));
+size_t forward_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_t precision, bool transposed) {
+    return std::max(record_partial_bytes(g, nsets, nops, precision),
+                    triples_partial_bytes(g, nsets, nops, precision, transposed));
 }
 
 double* forward_part(Graph& g, int32_t nsets, int32_t nops, int32_t precision, const char* what, size_t* bytes) {
-    *bytes = forward_partial_bytes(g, nsets, nops, precision);
+    *bytes = forward_partial_bytes(g, nsets, nops, precision, what == nullptr);
     if (*bytes <= g.ws_part.bytes) return *bytes ? (double*)g.ws_part.ptr : nullptr;
     *bytes = what ? record_partial_bytes(g, nsets, nops, precision) : 0;
     return *bytes ? (double*)g.ws_part.need(*bytes, what) : nullptr;

@@ -60,10 +60,10 @@ void Workspace::release() {
 
 // Bytes of partial rows in triple space for the layout and every smaller number
 // of sets: fewer sets may be on the products' side of the line where more are not.
-static size_t triples_reserve_bytes(const Graph& g, int64_t nsets, int64_t nops, int prec) {
-    size_t b = triples_partial_bytes(g, nsets, nops, prec);
+static size_t triples_reserve_bytes(const Graph& g, int64_t nsets, int64_t nops, int prec, bool transposed) {
+    size_t b = triples_partial_bytes(g, nsets, nops, prec, transposed);
     for (int64_t n : {32, 16, 8, 4, 1})
-        if (n < nsets) b = std::max(b, triples_partial_bytes(g, n, nops, prec));
+        if (n < nsets) b = std::max(b, triples_partial_bytes(g, n, nops, prec, transposed));
     return b;
 }
 
@@ -74,7 +74,7 @@ void reserve_shape(Graph& g, int64_t nsets, int64_t nops, int64_t ckpt_every, ui
         const size_t rec = record_partial_bytes(g, (int32_t)nsets, (int32_t)nops, prec);
         area = area || rec > 0;
         if (what & (CUT_RESERVE_APPLY | CUT_RESERVE_DERIV)) part = std::max(part, rec);
-        if (extra) tri = std::max(tri, triples_reserve_bytes(g, nsets, nops, prec));
+        if (extra) tri = std::max(tri, triples_reserve_bytes(g, nsets, nops, prec, (what & (CUT_RESERVE_DERIV | CUT_RESERVE_ADJOINT)) != 0));
         if (what & CUT_RESERVE_DERIV)
             deriv = std::max({deriv, jvp_ws_bytes(g, nsets, nops, prec), vjp_ws_bytes(g, nsets, nops, prec)});
         if (what & CUT_RESERVE_FLOW)

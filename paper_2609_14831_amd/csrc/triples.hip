@@ -334,37 +334,73 @@ static bool tri_reach(const Graph& g, int64_t ld, bool f64) { return g.N * ld * 
 // FP64 and the compensated float modes (the sums are FP64 with exact products,
 // at least as accurate as either); 32-bit offsets into both operand arrays.
 // Every launch costs a fixed latency (two kernels, at least m / 4 dependent
-// steps of 1.6 us), which the records' E x columns have to outweigh; the
-// segment kernel is worst above 32 sets (64 lanes) and best at float with 2 to
-// 16 sets.  One action of 3 operands, us, segment kernel -> triples:
-//   above the line  14 modes x 33 sets FP64 78 -> 38, float 56 -> 35
-//                   20 x 32 FP64 84 -> 62;  24 x 8 FP64 69 -> 52
-//                   24 x 1 FP64 40 -> 31;  26 x 4 float 52 -> 52;  26 x 2 FP64 58 -> 53
-//   below it        20 x 8 FP64 0.96 of its speed, 24 x 16 float 0.97
-//                   with 5 operands  22 x 8 float 43 -> 56;  24 x 4 FP64 66 -> 71
-static bool tri_faster(const Graph& g, int w, bool f64) {
-    const int least = w > 32 ? kTriMinModes : f64 && w > 16 ? 20 : w == 1 || w > (f64 ? 4 : 16) ? 24 : 26;
-    return g.tri.m >= least;
+// steps of 1.6 us), which the records' E x columns have to outweigh.  Up to 32
+// sets the segment kernel's lanes are full and it is best at float with 2 to 16
+// sets; above, its groups of 64 lanes are worst just past 32 and 64 sets, unless
+// the tiling gives it narrower groups or stages rows in LDS (`tuned`, what
+// cut_graph_autotune finds there).  The products run whole blocks of 16 sets and
+// column tiles of 16 modes, so 16 modes are better for them than 18.  One action,
+// us, records -> products (F: F32X, C: F32C):
+//   up to 32 sets, modes x sets x operands
+//     above the line  24x1x3 FP64 40 -> 31;  24x8x3 FP64 54 -> 30;  20x17x3 FP64 70 -> 44
+//                     26x2x2 F 25 -> 17;  26x8x8 C 70 -> 66;  24x17x5 C 81 -> 76;  24x32x5 F 93 -> 88
+//     below it        24x4x3 FP64 0.93 of its speed;  24x17x8 C 122 -> 131;  24x32x5 C 85 -> 88
+//   above 32, default tiling
+//     above the line  14x33x2 C 1.44, 14x64x6 F 1.09, 18x33x8 C 1.36, 18x64x4 F 1.04 times
+//     below it        18x64x6 F 78 -> 86;  18x128x6 F 111 -> 132
+//   above 32, tuned
+//     above the line  14x100x4 FP64 1.28, 16x33x1 FP64 1.46, 18x48x5 FP64 1.06, 16x49x8 C 1.05,
+//                     20x48x2 C 1.01, 20x128x4 C 1.01, 22x64x5 C 1.02 times
+//     below it        14x48x8 C 25 -> 57, 14x33x4 FP64 0.66, 16x48x8 C 0.85, 18x64x5 C 0.56,
+//                     20x64x5 F 0.89, 22x64x8 C 0.96 of its speed
+// The transposed actions' passes over the records have neither chunks nor narrow
+// groups: the line of the default tiling, for any number of operands (a VJP of 2
+// FP64 operands 1.1 to 4.8 times faster wherever it is taken).
+static bool tri_faster(const Graph& g, int w, int64_t nops, int32_t precision, bool transposed) {
+    const int m = g.tri.m;
+    const bool f64 = precision == CUT_F64;
+    if (w <= 32) {
+        int least = f64 && w > 16 ? 20 : w == 1 || w > (f64 ? 4 : 16) ? 24 : 26;
+        if (!f64 && w > 16 && !transposed && nops > (precision == CUT_F32C ? 4 : 5)) least = 26;
+        return m >= least;
+    }
+    if (transposed) return m >= kTriMinModes;
+    const bool tuned = g.bchunk != 0 || g.use_tiles || g.use_quadblocks;
+    const int last = (w - 1) % 64 + 1;  // sets in the last group of 64 lanes
+    if (!tuned) return m >= kTriMinModes && (f64 || m != 18 || nops <= 4 || last <= (w > 64 ? 32 : 48));
+    if (f64) return m >= 16 || w > 64;
+    if (m >= 22) return m > 22 || nops <= 5 || w <= 48 || w > 64;
+    return m == 20 ? nops <= 4 && (w <= 48 || w > 64) : m == 16 && w > 48;
 }
 
-// None where no pass over the layout is on the products' side of the line: their
-// widths are min(8, nsets) to nsets, and from there on the line falls with width.
-size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops, int32_t precision) {
-    const bool f64 = precision == CUT_F64;
-    if (!g.tri.ok || precision == CUT_F32 || !tri_reach(g, nops * nsets, f64)) return 0;
-    return tri_faster(g, (int)nsets, f64) ? tri_column_bytes(g) * (size_t)(nops * nsets) : 0;
+// fn(w) for a width of each kind on either side of the line among those of the
+// passes over a layout (min(8, nsets) to nsets)
+template <class F>
+static bool tri_any_width(int64_t nsets, F fn) {
+    const int64_t lo = std::min<int64_t>(8, nsets);
+    for (int64_t w : {lo, (int64_t)17, (int64_t)33, (int64_t)49, (int64_t)65, nsets})
+        if (w >= lo && w <= nsets && fn((int)w)) return true;
+    return false;
+}
+
+size_t triples_partial_bytes(const Graph& g, int64_t nsets, int64_t nops, int32_t precision, bool transposed) {
+    if (!g.tri.ok || precision == CUT_F32 || !tri_reach(g, nops * nsets, precision == CUT_F64)) return 0;
+    const bool any = tri_any_width(nsets, [&](int w) {
+        return tri_faster(g, w, nops, precision, false) || (transposed && tri_faster(g, w, nops, precision, true));
+    });
+    return any ? tri_column_bytes(g) * (size_t)(nops * nsets) : 0;
 }
 
 bool triples_always(const Graph& g, int64_t nsets, int64_t nops, int32_t precision) {
-    const bool f64 = precision == CUT_F64;
-    if (!g.tri.ok || precision == CUT_F32 || !tri_reach(g, nops * nsets, f64)) return false;
-    return tri_faster(g, (int)std::min<int64_t>(8, nsets), f64);
+    if (!g.tri.ok || precision == CUT_F32 || !tri_reach(g, nops * nsets, precision == CUT_F64)) return false;
+    return !tri_any_width(nsets, [&](int w) { return !tri_faster(g, w, nops, precision, false); });
 }
 
 bool triples_usable(const Graph& g, const PassArgs& a) {
     if (!g.tri.ok || a.precision == CUT_F32) return false;
-    const bool f64 = a.precision == CUT_F64;
-    if (!tri_faster(g, tri_width(a), f64) || !tri_reach(g, std::max({a.lda, a.ldb, a.ldfull}), f64)) return false;
+    const bool transposed = a.csr != &g.csr[0][0];
+    if (!tri_faster(g, tri_width(a), a.nops, a.precision, transposed)) return false;
+    if (!tri_reach(g, std::max({a.lda, a.ldb, a.ldfull}), a.precision == CUT_F64)) return false;
     return a.part_bytes >= tri_column_bytes(g) * (size_t)((int64_t)a.nops * a.nsets);
 }
 

@@ -292,3 +292,28 @@ L.cut_flow_integrate(g, p, {nsets}, 1, [2] * {nsets}, Buf(1), stream=0x11, reser
 out([k for k, _ in kernels(log())])
 """)
     assert ("k_flow_small" in ks) == small and ("k_pass" in ks) == (not small)
+
+
+@pytest.mark.parametrize("m,nsets,nops,prec,flags,products", [
+    # up to 32 sets
+    (24, 1, 8, "F64", 0, True), (24, 4, 3, "F64", 0, False), (24, 8, 3, "F64", 0, True), (20, 17, 8, "F64", 0, True),
+    (18, 17, 1, "F64", 0, False), (24, 16, 1, "F32X", 0, False), (24, 32, 5, "F32X", 0, True), (24, 32, 6, "F32X", 0, False),
+    (24, 17, 4, "F32C", 0, True), (24, 17, 5, "F32C", 0, False), (26, 2, 8, "F32C", 0, True), (26, 32, 8, "F32C", 0, True),
+    # above, default tiling
+    (14, 33, 8, "F32C", 0, True), (18, 48, 8, "F32X", 0, True), (18, 49, 5, "F32X", 0, False), (18, 64, 4, "F32C", 0, True),
+    (18, 65, 8, "F32X", 0, True), (18, 128, 5, "F32X", 0, False), (18, 64, 8, "F64", 0, True), (20, 64, 8, "F32C", 0, True),
+    # above, B-chunk 32 or LDS tiles
+    (14, 64, 1, "F64", 32, False), (14, 65, 1, "F64", 32, True), (14, 100, 2, "F32X", 32, False), (16, 48, 1, "F32X", 32, False),
+    (16, 49, 8, "F32C", 32, True), (16, 33, 3, "F64", 2, True), (18, 100, 2, "F32C", 32, False), (18, 33, 8, "F64", 16, True),
+    (20, 48, 4, "F32C", 32, True), (20, 48, 5, "F32C", 32, False), (20, 64, 1, "F32X", 2, False), (20, 65, 4, "F32X", 32, True),
+    (22, 64, 5, "F32C", 32, True), (22, 64, 6, "F32C", 32, False), (22, 48, 8, "F32X", 32, True), (24, 64, 8, "F32C", 32, True),
+])
+def test_actions_take_products_on_their_side_of_the_line(m, nsets, nops, prec, flags, products):
+    ks = H.run(f"""
+g = graph({m})
+L.cut_graph_set_tiling(g, 1024, 512, {flags})
+log()
+L.cut_graph_apply(g, 0, L.CUT_{prec}, {nsets}, {nops}, Buf({nsets}), Buf({nsets * nops}), Buf({nsets * nops}), stream=0x11)
+out([k for k, _ in kernels(log())])
+""")
+    assert any(k.startswith("k_triples") for k in ks) == products, ks
