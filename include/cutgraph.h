@@ -455,7 +455,8 @@ cut_status cut_flow_adjoint(cut_graph_t g, const cut_flow_params* p, int64_t nse
  * operand or the target, which makes that region small); the chunk sums are
  * kept as partial rows and added in chunk order.  Other passes split a long
  * target over the four wavefronts of a workgroup.  Shorter targets are packed
- * four to a workgroup, one per wavefront.
+ * four to a workgroup, one per wavefront.  (The complex records of Pauli-boson
+ * graphs keep thresholds of their own: 512 for E_L, 1024 for the others.)
  * CUT_TILE_XCD_REMAP: consecutive chunk and task ranges run on one XCD (one L2).
  * CUT_TILE_NO_CHUNKS: no chunked form.
  * CUT_TILE_TRIPLE_CHUNKS (Majorana graphs): every quartic target K is also cut,

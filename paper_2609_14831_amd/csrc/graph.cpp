@@ -329,9 +329,10 @@ static void build_qb_tiling(Graph& g, const DevCSR& c) {
 
 // Records of a complex-record target of E_L above which it is split over a
 // workgroup: a wavefront's chain of 1024 records outlasts the launch's other
-// work where there are few targets.  10 steps of 8 operators, us, 1024 -> 512:
-// modes x degree 4 x 4 (1980 targets) 1531 -> 1420, 3 x 4 852 -> 802, 2 x 4 676 ->
-// 641; 256 gains no more and costs 7 % with 4 operators on 336 targets.
+// work where there are few targets.  10 steps of 8 operators at modes x degree 4 x 4
+// (1980 targets), a whole call, us, 1024 -> 512: 1746 -> 1642; one action of 8 at 3 x 4
+// 14 -> 12, at 2 x 4 10 -> 9; 256 gains no more and costs 7 % with 4 operators on 336
+// targets.  cut_graph_set_tiling does not rebuild these lists.
 constexpr int64_t kComplexSplit = 512;
 
 void build_tasks(Graph& g, DevCSR& c) {

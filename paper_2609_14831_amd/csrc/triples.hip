@@ -342,11 +342,14 @@ static bool tri_reach(const Graph& g, int64_t ld, bool f64) { return g.N * ld * 
 // column tiles of 16 modes, so 16 modes are better for them than 18.  One action,
 // us, records -> products (F: F32X, C: F32C):
 //   up to 32 sets, modes x sets x operands
-//     above the line  24x1x3 FP64 40 -> 31;  24x8x3 FP64 54 -> 30;  20x17x3 FP64 70 -> 44
-//                     26x2x2 F 25 -> 17;  26x8x8 C 70 -> 66;  24x17x5 C 81 -> 76;  24x32x5 F 93 -> 88
-//     below it        24x4x3 FP64 0.93 of its speed;  24x17x8 C 122 -> 131;  24x32x5 C 85 -> 88
+//     above the line  24x1x3 FP64 25 -> 17;  24x8x3 FP64 53 -> 29;  20x17x3 FP64 68 -> 32
+//                     26x2x2 F 30 -> 20;  26x8x8 C 81 -> 77;  24x17x4 C 74 -> 64;  24x32x5 F 93 -> 88
+//     below it        18x8x3 C 11 -> 20;  20x4x3 FP64 16 -> 24;  22x16x5 C 36 -> 47;  24x24x8 C 125 -> 137
+//                     (but 22x16x3 FP64 59 -> 37 and 24x8x3 C 32 -> 26: products of 24 modes with 2
+//                     to 16 float sets are 1.06 to 1.5 times faster, of 22 with 8 or 16 FP64 sets
+//                     1.04 to 1.7, of 16 with 17 to 32 FP64 sets 1.5 to 1.9)
 //   above 32, default tiling
-//     above the line  14x33x2 C 1.44, 14x64x6 F 1.09, 18x33x8 C 1.36, 18x64x4 F 1.04 times
+//     above the line  14x33x3 FP64 62 -> 32, F 41 -> 26;  14x64x6 F 1.09, 18x33x8 C 1.36, 18x64x4 F 1.04 times
 //     below it        18x64x6 F 78 -> 86;  18x128x6 F 111 -> 132
 //   above 32, tuned
 //     above the line  14x100x4 FP64 1.28, 16x33x1 FP64 1.46, 18x48x5 FP64 1.06, 16x49x8 C 1.05,
@@ -666,11 +669,11 @@ size_t outside_partial_bytes(const Graph& g, int64_t nsets, int64_t nops) {
 
 // The products do 1.9 (24 modes) to 4 (16) times the records' operations on the
 // padding of their tiles, and every tile is a chain of 3 m / 4 steps; the records are
-// streamed once per column group of the segment kernel.  One action, us,
-// segment kernel -> products:
-//   above the line  24 modes, 8 sets x 3 operands FP64 835 -> 323, 16 x 3 float 1.5 times faster
-//                   22 x 1 x 3 FP64 1.2, 20 x 4 x 3 float 1.1, 18 x 8 x 3 FP64 1.07 times
-//   below it        20 x 1 x 3 FP64 0.89 of its speed, 18 x 8 x 3 float 0.85, 16 x 8 x 3 FP64 0.76
+// streamed once per column group of the segment kernel.  One action, us, segment
+// kernel -> products (with the 4 us that putting their partial rows in order costs):
+//   above the line  24 modes, 8 sets x 3 operands FP64 833 -> 302, 16 x 3 float 649 -> 438
+//                   22 x 1 x 3 FP64 169 -> 136, 20 x 4 x 3 float 83 -> 71, 18 x 8 x 3 FP64 80 -> 74
+//   below it        20 x 1 x 3 FP64 79 -> 86, 18 x 8 x 3 float 42 -> 56, 18 x 4 x 3 FP64 48 -> 61, 16 x 8 x 3 30 -> 46
 bool outside_usable(const Graph& g, const PassArgs& a) {
     const int least = a.nsets == 1 ? 22 : a.precision == CUT_F64 && a.nsets > 4 ? 18 : 20;
     if (!g.tri.out_ok || g.tri.m < least || a.precision == CUT_F32) return false;
