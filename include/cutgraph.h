@@ -37,11 +37,10 @@
  *    VJP, derivatives, flows) must not overlap in time on one handle: issue
  *    them on one stream, or load the bundle once per stream.  The other calls
  *    may overlap: outside-space actions, forward actions none of whose targets
- *    is split, adjoint actions, generators.  Where such an action contracts
- *    over products of strings instead of records (one coefficient set from 22
- *    to 24 modes, more from 14 to 20, by width) it keeps partial rows in an
- *    area of the handle whose uses are put in order on the device: on two
- *    streams they run one after the other.  Under stream capture it runs on
+ *    is split, adjoint actions, generators.  Where such an action runs as
+ *    products in triple space instead of over its records it keeps partial rows
+ *    in an area of the handle whose uses are put in order on the device: on two
+ *    streams they run one after the other.  Under stream capture it runs over
  *    the records, without them.  Setup calls
  *    (reserve, set_tiling, autotune, free) must not run concurrently with any
  *    other call on the handle.
