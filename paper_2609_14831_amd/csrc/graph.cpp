@@ -108,6 +108,7 @@ Graph::~Graph() {
     ws.release();
     ws_small.release();
     ws_part.release();
+    ws_prod.release();
     ws_tri.release();
     ws_deriv.release();
     rows.release();

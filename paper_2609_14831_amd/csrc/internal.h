@@ -375,7 +375,8 @@ struct Graph {
     int64_t max_lds = 65536;         // LDS bytes one workgroup may allocate
     Workspace ws;                    // flow state and stage storage
     Workspace ws_small;              // scratch of single generator-VJP calls
-    Workspace ws_part;               // partial rows of single forward passes
+    Workspace ws_part;               // partial rows of single forward passes over the records
+    Workspace ws_prod;               // partial rows of single passes in triple space (none: they run on the records)
     Workspace ws_tri;                // partial rows of flows in triple space (none: their passes run on the records)
     Workspace ws_deriv;              // generator, tangent and float shadows of derivative calls
     SharedRows rows;                 // outside-space actions; forward actions without partial rows over the records
@@ -474,8 +475,8 @@ bool forward_set_ranges(const Graph& g, const PassArgs& a);
 // forward pass of this shape runs in)
 size_t record_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_t precision);
 
-// the partial rows of a pass outside flows: the reserved area when it holds
-// every route's, else what the records alone need (`what` names the call that
+// the partial rows of a pass outside flows: those of every route where they are
+// there, else what the records alone need (`what` names the call that
 // fails without them; null: a VJP, which runs without partial rows then)
 double* forward_part(Graph& g, int32_t nsets, int32_t nops, int32_t precision, const char* what, size_t* bytes);
 

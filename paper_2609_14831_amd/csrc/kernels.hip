@@ -1458,7 +1458,8 @@ size_t forward_partial_bytes(const Graph& g, int32_t nsets, int32_t nops, int32_
 
 double* forward_part(Graph& g, int32_t nsets, int32_t nops, int32_t precision, const char* what, size_t* bytes) {
     *bytes = forward_partial_bytes(g, nsets, nops, precision, what == nullptr);
-    if (*bytes <= g.ws_part.bytes) return *bytes ? (double*)g.ws_part.ptr : nullptr;
+    if (*bytes && *bytes <= g.ws_prod.bytes && triples_partial_bytes(g, nsets, nops, precision, what == nullptr))
+        return (double*)g.ws_prod.ptr;
     *bytes = what ? record_partial_bytes(g, nsets, nops, precision) : 0;
     return *bytes ? (double*)g.ws_part.need(*bytes, what) : nullptr;
 }

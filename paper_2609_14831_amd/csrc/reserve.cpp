@@ -91,9 +91,11 @@ void reserve_shape(Graph& g, int64_t nsets, int64_t nops, int64_t ckpt_every, ui
     g.ws_deriv.reserve(deriv);
     g.ws.reserve(ws);
     if (!extra) return;
-    // partial rows of products: without them the same calls run on the records
+    // partial rows of products, in areas of their own (growing them moves none that
+    // a captured pass over the records points into): without them the same calls run
+    // on the records
     const bool apply = (what & CUT_RESERVE_APPLY) != 0;
-    if (tri > 0 && ((apply && area) || (what & CUT_RESERVE_DERIV))) g.ws_part.reserve_optional(std::max(part, tri));
+    if (tri > 0 && ((apply && area) || (what & CUT_RESERVE_DERIV))) g.ws_prod.reserve_optional(std::max(part, tri));
     if (tri > 0 && (what & (CUT_RESERVE_FLOW | CUT_RESERVE_ADJOINT))) g.ws_tri.reserve_optional(std::max(part, tri));
     if (apply) g.rows.reserve_optional(std::max(outside, area ? 0 : tri));
 }
@@ -155,6 +157,6 @@ extern "C" cut_status cut_graph_reserved_bytes(cut_graph_t h, int64_t* bytes) {
     ABI_BEGIN
     Graph& g = checked(h);
     if (!bytes) CUT_FAIL(CUT_E_INVAL, "cut_graph_reserved_bytes: null output");
-    *bytes = (int64_t)(g.ws.bytes + g.ws_small.bytes + g.ws_part.bytes + g.ws_tri.bytes + g.ws_deriv.bytes + g.rows.ws.bytes);
+    *bytes = (int64_t)(g.ws.bytes + g.ws_small.bytes + g.ws_part.bytes + g.ws_prod.bytes + g.ws_tri.bytes + g.ws_deriv.bytes + g.rows.ws.bytes);
     ABI_END
 }

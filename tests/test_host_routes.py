@@ -317,3 +317,21 @@ L.cut_graph_apply(g, 0, L.CUT_{prec}, {nsets}, {nops}, Buf({nsets}), Buf({nsets 
 out([k for k, _ in kernels(log())])
 """)
     assert any(k.startswith("k_triples") for k in ks) == products, ks
+
+
+def test_optional_rows_never_move_the_records_own():
+    """Rows of products that become affordable later grow beside the area that passes over the
+    records use, whose address a captured graph may hold."""
+    out = H.run("""
+g = graph(24)
+fake.fake_left(1 << 20)
+log()
+L.cut_graph_reserve(g, 8, 3, 0, L.CUT_RESERVE_APPLY)
+first = log()
+fake.fake_left(1 << 40)
+L.cut_graph_reserve(g, 8, 2, 0, L.CUT_RESERVE_APPLY)     # a smaller shape
+out([first, log()])
+""")
+    first, later = out
+    assert any(l.startswith("malloc") for l in first) and any(l.startswith("malloc") for l in later)
+    assert not any(l.startswith("free") for l in later), later
