@@ -660,13 +660,6 @@ void build_outside(Graph& g, const HostGraph& hg) {
 // time as fit 2 GiB (0: not even one does).
 size_t outside_least(const Graph& g, int64_t nsets) { return (size_t)(4 * g.n_out * nsets) * sizeof(double); }
 
-size_t outside_partial_bytes(const Graph& g, int64_t nsets, int64_t nops) {
-    constexpr size_t kCap = (size_t)2 << 30;
-    if (!g.tri.out_ok) return 0;
-    const size_t one = outside_least(g, nsets);
-    return one > kCap ? 0 : one * std::min<size_t>((size_t)nops, kCap / one);
-}
-
 // The products do 1.9 (24 modes) to 4 (16) times the records' operations on the
 // padding of their tiles, and every tile is a chain of 3 m / 4 steps; the records are
 // streamed once per column group of the segment kernel.  One action, us, segment
@@ -674,11 +667,22 @@ size_t outside_partial_bytes(const Graph& g, int64_t nsets, int64_t nops) {
 //   above the line  24 modes, 8 sets x 3 operands FP64 833 -> 302, 16 x 3 float 649 -> 438
 //                   22 x 1 x 3 FP64 169 -> 136, 20 x 4 x 3 float 83 -> 71, 18 x 8 x 3 FP64 80 -> 74
 //   below it        20 x 1 x 3 FP64 79 -> 86, 18 x 8 x 3 float 42 -> 56, 18 x 4 x 3 FP64 48 -> 61, 16 x 8 x 3 30 -> 46
+static bool outside_faster(const Graph& g, int64_t nsets, bool f64) {
+    return g.tri.m >= (nsets == 1 ? 22 : f64 && nsets > 4 ? 18 : 20);
+}
+
+size_t outside_partial_bytes(const Graph& g, int64_t nsets, int64_t nops) {
+    constexpr size_t kCap = (size_t)2 << 30;
+    // FP64's side of the line holds the floats', whose rows reach further
+    if (!g.tri.out_ok || !outside_faster(g, nsets, true) || !tri_reach(g, nops * nsets, false)) return 0;
+    const size_t one = outside_least(g, nsets);
+    return one > kCap ? 0 : one * std::min<size_t>((size_t)nops, kCap / one);
+}
+
 bool outside_usable(const Graph& g, const PassArgs& a) {
-    const int least = a.nsets == 1 ? 22 : a.precision == CUT_F64 && a.nsets > 4 ? 18 : 20;
-    if (!g.tri.out_ok || g.tri.m < least || a.precision == CUT_F32) return false;
-    const int64_t esz = a.precision == CUT_F64 ? 8 : 4;
-    return g.N * std::max(a.lda, a.ldb) * esz < (int64_t)0x7FFFFFFF;
+    const bool f64 = a.precision == CUT_F64;
+    return g.tri.out_ok && a.precision != CUT_F32 && outside_faster(g, a.nsets, f64) &&
+           tri_reach(g, std::max(a.lda, a.ldb), f64);
 }
 
 void launch_outside(const Graph& g, const PassArgs& a, double* part, size_t bytes, hipStream_t s) {

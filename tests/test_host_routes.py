@@ -335,3 +335,16 @@ out([first, log()])
     first, later = out
     assert any(l.startswith("malloc") for l in first) and any(l.startswith("malloc") for l in later)
     assert not any(l.startswith("free") for l in later), later
+
+
+@pytest.mark.parametrize("m,nsets,rows", [(18, 4, False), (18, 5, True), (20, 1, False), (20, 2, True)])
+def test_outside_rows_only_where_the_products_can_run(m, nsets, rows):
+    sizes, ks = H.run(f"""
+g = graph({m}, L.CUT_BUILD_OUTSIDE)
+log()
+L.cut_graph_apply(g, 2, L.CUT_F64, {nsets}, 2, Buf({nsets}), Buf({2 * nsets}), Buf({2 * nsets}), stream=0x11)
+lines = log()
+out([[int(l.split()[1]) for l in lines if l.startswith("malloc")], [k for k, _ in kernels(lines)]])
+""")
+    n_out = {18: 18564, 20: 38760}[m]
+    assert (4 * n_out * 2 * nsets * 8 in sizes) == rows and ("k_outside" in ks) == rows
